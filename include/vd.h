@@ -91,7 +91,10 @@ typedef struct {
                                  site cache, the box is first cut by the bisectors of the
                                  Delaunay neighbours that the cached sites certify (an empty
                                  sphere through v_i and the neighbour), which are faces of
-                                 the cell.  Both modes give the same pieces. */
+                                 the cell.  Both modes give the same pieces.  With the other
+                                 search options at their defaults (and no monitor) the box is
+                                 instead cut by the nearby sites in order of distance, all its
+                                 corners tested against one site at a time. */
   int32_t no_sync;            /* 1: vd_clip_cells only enqueues work (no host synchronisation,
                                  no allocation), so it can be captured into a HIP graph.
                                  Needs a handle sized by an earlier synchronous clip of the
@@ -315,7 +318,9 @@ void vd_cells_free(vd_cells c);
 
 typedef struct {
   int64_t n_sites, n_pieces, n_faces, n_verts, n_nbrs;
-  int64_t nn_queries;  /* point-in-cell tests (nearest-site queries) performed */
+  int64_t nn_queries;  /* point-in-cell tests (nearest-site queries) performed; the default
+                          3D clip, which tests all corners against the sites in order of
+                          distance, counts the corners left after that and the grid queries */
   int64_t clips;       /* clips applied */
   int64_t candidates;  /* sites examined by the nearest-site queries */
   int64_t grid_queries; /* queries not answered by the per-wave site cache (0 for surfaces) */

@@ -620,6 +620,7 @@ hipError_t alloc_cells(vd_cells c, int64_t n, const Caps &want) {
     t = 0; if ((e = ensure(d.pstart, t, n)) != hipSuccess) return e;
     t = 0; if ((e = ensure(d.nstart, t, n)) != hipSuccess) return e;
     t = 0; if ((e = ensure(d.seed, t, n)) != hipSuccess) return e;
+    t = 0; if ((e = ensure(d.redo, t, n)) != hipSuccess) return e;
     t = 0; if ((e = ensure(c->piece_off, t, n + 1)) != hipSuccess) return e;
     t = 0; if ((e = ensure(c->nbr_off, t, n + 1)) != hipSuccess) return e;
     t = 0; if ((e = ensure(c->scan_tmp, t, n / 1024 + 2)) != hipSuccess) return e;
@@ -627,7 +628,7 @@ hipError_t alloc_cells(vd_cells c, int64_t n, const Caps &want) {
     c->cap_n = n;
   }
   if ((e = ensure_fixed(d.cnt, CNT_N)) != hipSuccess) return e;
-  if ((e = ensure_fixed(d.queue, VD_QUEUES * VD_QSTRIDE)) != hipSuccess) return e;
+  if ((e = ensure_fixed(d.queue, (VD_QREDO + 1) * VD_QSTRIDE)) != hipSuccess) return e;
   if (!c->host_cnt) {
     if ((e = hipHostMalloc((void **)&c->host_cnt, sizeof(unsigned long long) * CNT_N, hipHostMallocDefault)) !=
         hipSuccess)
@@ -845,15 +846,20 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     return r;
   };
   Caps want;
-  // a site's cell meets a few simplices when simplices and cells are alike in
-  // size, many when simplices are much smaller: 8 per site plus 3 per simplex
-  want.piece = std::max<int64_t>(c->d.cap_piece, 8 * n + 3 * dom->m + 1024);
+  // first sizes.  n convex cells and m simplices that overlay each other meet in
+  // about n + m + 6 (n^2/3 m^1/3 + n^1/3 m^2/3) pieces (the two cross terms come
+  // from cells crossing simplex faces and simplices crossing cell faces; 5.4 to
+  // 5.7 was measured on uniform sites); of their faces 15.5 per cell and 4.2 per
+  // cut are on bisectors.  A quarter more for the ends of the waves' chunks.
+  const double cn = (double)n, cm = (double)dom->m;
+  const double pieces = dom->dim == 3 ? cn + cm + 6.0 * (std::cbrt(cn * cn * cm) + std::cbrt(cn * cm * cm)) : 0.0;
+  want.piece = std::max<int64_t>(c->d.cap_piece, std::max<int64_t>(8 * n + 3 * dom->m + 1024, (int64_t)(1.25 * pieces) + 1024));
   want.nbr = std::max<int64_t>(c->d.cap_nbr, 20 * n + 1024);
   // surfaces always keep the edge flags of their pieces (the per-site pass reads them)
   const bool keep_faces = opt.emit_polytopes || dom->dim == 2;
   want.face = keep_faces ? std::max<int64_t>(c->d.cap_face, 10 * want.piece) : 0;
   want.vert = keep_faces ? std::max<int64_t>(c->d.cap_vert, 16 * want.piece) : 0;
-  want.fint = opt.want_grad ? std::max<int64_t>(c->d.cap_fint, 4 * want.piece) : 0;
+  want.fint = opt.want_grad ? std::max<int64_t>(c->d.cap_fint, std::max<int64_t>(4 * want.piece, (int64_t)(1.25 * (15.5 * cn + 4.2 * pieces)) + 1024)) : 0;
   if (opt.no_sync) {
     // no allocation: the arenas keep the sizes of the synchronous clip before
     want.piece = c->d.cap_piece; want.nbr = c->d.cap_nbr;
@@ -883,17 +889,24 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     // persistent 3D kernel: each wave reserves output chunks of about 1/8 of an
     // arena's share per wave, so unused chunk tails stay within 1/8 of it
     const int64_t items = dom->dim == 3 ? n : dom->m;  // sites, or triangles
-    const int wg = dom->dim == 3 ? vd_sites3d_workgroups(n) : vd_surface_workgroups(dom->m);
+    // the default search goes to the sweep kernel, the variants of the paper's
+    // search, its counters and the per-simplex carve to the general one
+    const bool sweep = dom->dim == 3 && d.mode == 1 && (d.cache || g->power) && !d.improved && !d.straddle && !d.monitor;
+    const int wg = dom->dim == 2 ? vd_surface_workgroups(dom->m) : sweep ? vd_sweep_workgroups(n) : vd_sites3d_workgroups(n);
+    // per-wave scratch of either kernel (a later no-sync clip may take the other)
+    const int wgen = dom->dim == 3 ? vd_sites3d_workgroups(n) : 0;
+    const int wgs = dom->dim == 3 ? std::max(vd_sweep_workgroups(n), wgen) : 0;
     if (dom->dim == 3 &&
-        (c->cap_spill < wg || d.q_spill < c->q_spill_want || d.nbs_cap < c->nb_spill_want)) {
+        (c->cap_spill < wgs || d.q_spill < c->q_spill_want || d.nbs_cap < c->nb_spill_want)) {
       if (opt.no_sync) return bail(fail(VD_ERR_INVALID_ARG, "vd_clip_cells: no_sync on an unsized handle"));
-      const int64_t w = std::max<int64_t>(wg, c->cap_spill);
+      const int64_t w = std::max<int64_t>(wgs, c->cap_spill);
+      c->cap_gen = std::max<int64_t>(wgen, c->cap_gen);
       int64_t t = 0;
-      HIP_TRY(ensure(d.tq_spill, t, w * c->q_spill_want));
+      HIP_TRY(ensure(d.tq_spill, t, w * (c->q_spill_want + VD_Q_MAX)));
       t = 0;
-      HIP_TRY(ensure(d.nb_spill, t, w * c->nb_spill_want));
+      HIP_TRY(ensure(d.nb_spill, t, c->cap_gen * c->nb_spill_want));
       t = 0;
-      HIP_TRY(ensure(d.saved, t, w * VD_SAVE_DOUBLES));
+      HIP_TRY(ensure(d.saved, t, c->cap_gen * VD_SAVE_DOUBLES));
       c->cap_spill = w;
       d.q_spill = c->q_spill_want;
       d.nbs_cap = c->nb_spill_want;
@@ -1010,11 +1023,16 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     }
     if (dom->dim == 2) vd_launch_fill_int(d.pcount, n, 0, st);
     if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev0, st));
-    if (dom->dim == 3) vd_launch_sites3d(G, D, c->d_dev, wg, opt.monitor != 0, opt.use_density != 0, g->power, d.whole == 2, st);
+    if (sweep) vd_launch_sweep(G, D, c->d_dev, wg, opt.use_density != 0, g->power, d.whole == 2, c->used_bseeds, st);
+    else if (dom->dim == 3) vd_launch_sites3d(G, D, c->d_dev, wg, opt.monitor != 0, opt.use_density != 0, g->power, d.whole == 2, false, st);
     else vd_launch_surface(G, D, c->d_dev, wg, opt.use_density != 0, g->power, st);
     if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev1, st));
     HIP_TRY(hipGetLastError());
+    // the sites the sweep left (usually none; a no-sync clip cannot look)
+    const int wredo = std::min(wg, std::min(512, vd_sites3d_workgroups(n)));
     if (opt.no_sync) {
+      if (sweep) vd_launch_void_pieces(c->d_dev, st);
+      if (sweep) vd_launch_sites3d(G, D, c->d_dev, wredo, false, opt.use_density != 0, g->power, d.whole == 2, true, st);
       // stream-ordered only: finalize from the device counters, copy them to
       // pinned host memory, and check them in vd_cells_info
       c->pending = true;
@@ -1029,6 +1047,13 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     }
     HIP_TRY(hipMemcpyAsync(c->host_cnt, d.cnt, sizeof(unsigned long long) * CNT_N, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
+    if (sweep && c->host_cnt[CNT_REDO]) {
+      vd_launch_void_pieces(c->d_dev, st);
+      vd_launch_sites3d(G, D, c->d_dev, wredo, false, opt.use_density != 0, g->power, d.whole == 2, true, st);
+      if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev1, st));
+      HIP_TRY(hipMemcpyAsync(c->host_cnt, d.cnt, sizeof(unsigned long long) * CNT_N, hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipStreamSynchronize(st));
+    }
     c->carve_ms = c->split_ms = -1.0;
     if (opt.time_kernels) {
       float ms = 0.f;
@@ -1048,11 +1073,11 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     if (grow) { want = need; continue; }
     if (dom->dim == 3 && hc[CNT_ERR_CAP] && !hc[CNT_ERR_DEG] && !hc[CNT_ERR_LOC]) {
       // a cell that meets more tetrahedra, or has more neighbours, than the
-      // per-wave overflow buffers hold: grow them (within about 4 GB each) and
+      // per-wave overflow buffers hold: grow them (within about 8 GB each) and
       // run again; the LDS capacities of the polytope itself are fixed
       const unsigned long long stg = hc[CNT_STAGES];
       const unsigned long long growable = (1ull << VD_STAGE_SIMPLICES) | (1ull << VD_STAGE_NEIGHBOURS);
-      const int64_t wmax = std::max<int64_t>(1, (int64_t)(1ll << 30) / std::max<int64_t>(c->cap_spill, 1));
+      const int64_t wmax = std::max<int64_t>(1, (int64_t)(1ll << 31) / std::max<int64_t>(c->cap_spill, 1));
       bool regrow = !(stg & ~growable);
       if (regrow && (stg & (1ull << VD_STAGE_SIMPLICES))) {
         const int64_t nw = std::min<int64_t>({(int64_t)c->q_spill_want * 4, dom->m, wmax});
@@ -1114,7 +1139,7 @@ void vd_cells_free(vd_cells c) {
   if (c->ev0) hipEventDestroy(c->ev0);
   if (c->ev1) hipEventDestroy(c->ev1);
   if (c->ev2) hipEventDestroy(c->ev2);
-  hipFree(c->d_dev); hipFree(d.queue); hipFree(d.tq_spill); hipFree(d.saved);
+  hipFree(c->d_dev); hipFree(d.queue); hipFree(d.tq_spill); hipFree(d.redo); hipFree(d.saved);
   hipFree(c->outside);
   hipFree(d.nb_spill); hipFree(d.sq_spill); hipFree(c->order_buf);
   vd_cells_free(c->bcells);

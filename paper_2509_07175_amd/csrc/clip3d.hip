@@ -41,7 +41,7 @@
 // wave with butterfly shuffles (fixed order, no floating-point atomics).
 #include <type_traits>
 
-#include "vd_arena.h"
+#include "vd_site.h"
 
 namespace {
 
@@ -91,17 +91,7 @@ struct Stats {
   long long queries = 0, cands = 0, clips = 0, grid = 0;  // grid: queries not answered by the site cache
 };
 
-__device__ __forceinline__ int p8(int packed, int e) { return (packed >> (8 * e)) & 0xff; }
-__device__ __forceinline__ int pack3(int a, int b, int c) { return a | (b << 8) | (c << 16); }
-__device__ __forceinline__ uint64_t low_mask(int k) { return k >= 64 ? ~0ull : ((1ull << k) - 1ull); }
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-
-struct SiteCtx {
-  double vx, vy, vz, delta;
-  double h, w;  // power diagram: lifted coordinate and weight of the site (else 0)
-  int si;
-};
 
 // Vertex of three planes by Cramer's rule, planes taken in ascending flag order
 // so a vertex does not depend on the order in which its planes were created.
@@ -614,28 +604,6 @@ __device__ int carve(WaveLds &S, const GridView &G, const CarveParams C, const S
   return 3;
 }
 
-// Plane of face f of T_a (opposite vertex f), outward, relative to v_i, and
-// its flag.  Face loops {1,2,3},{0,3,2},{0,1,3},{0,2,1} are packed 2 bits per
-// vertex, 6 bits per face (no indexed local arrays).
-__device__ __forceinline__ void tet_plane(const DomainView &D, const SiteCtx &X, int a, int f, double *pl,
-                                          int &lab) {
-  const auto tv = &GL(D.simp)[(long long)a * 4];
-  const unsigned loops = (1u | 2u << 2 | 3u << 4) | (0u | 3u << 2 | 2u << 4) << 6 |
-                         (0u | 1u << 2 | 3u << 4) << 12 | (0u | 2u << 2 | 1u << 4) << 18;
-  const unsigned lf = loops >> (6 * f);
-  const auto pA = &GL(D.verts)[3 * (long long)tv[lf & 3]];
-  const auto pB = &GL(D.verts)[3 * (long long)tv[(lf >> 2) & 3]];
-  const auto pC = &GL(D.verts)[3 * (long long)tv[(lf >> 4) & 3]];
-  const double A0 = pA[0] - X.vx, A1 = pA[1] - X.vy, A2 = pA[2] - X.vz;
-  const double ab0 = pB[0] - pA[0], ab1 = pB[1] - pA[1], ab2 = pB[2] - pA[2];
-  const double ac0 = pC[0] - pA[0], ac1 = pC[1] - pA[1], ac2 = pC[2] - pA[2];
-  const double n0 = ab1 * ac2 - ab2 * ac1, n1 = ab2 * ac0 - ab0 * ac2, n2 = ab0 * ac1 - ab1 * ac0;
-  pl[0] = n0; pl[1] = n1; pl[2] = n2;
-  pl[3] = n0 * A0 + n1 * A1 + n2 * A2;
-  const int b = GL(D.adj)[(long long)a * 4 + f];
-  lab = b >= 0 ? -(b + 1) : VD_BND_BASE + f;
-}
-
 // P <- T_a: 4 planes (face f opposite vertex f), 4 corners.  Lane l < 4
 // builds plane l and corner l; the fixed topology of a positively oriented
 // tetrahedron is packed in constants.
@@ -799,8 +767,6 @@ __device__ void init_box(WaveLds &S, const SiteCtx &X, const double *lo, const d
   __syncthreads();
 }
 
-__device__ __forceinline__ int convert_label(const GridView &G, int lab) { return lab >= 0 ? GL(G.perm)[lab] : lab; }
-
 // Face moments of the bisector faces of the piece in LDS, for the adjoint:
 // for face x on B_ik, I0 = int y dA/d, I1 = int y y^T dA/d, I2 = int |y|^2 y dA/d
 // with y = x - v_i and d = |v_k - v_i|.  Lane x walks around face x from its
@@ -898,16 +864,16 @@ __device__ void face_moments(WaveLds &S, int nc, int npl, uint64_t fmask, const 
 // global buffer (cells that meet more simplices than the LDS queue holds).
 // Out of line: the common case never touches them.
 __device__ __forceinline__ int spill_get(const CellsDev &C, int i) {
-  return GL(C.tq_spill)[(long long)blockIdx.x * C.q_spill + i - VD_Q_MAX];
+  return GL(C.tq_spill)[(long long)blockIdx.x * (C.q_spill + VD_Q_MAX) + i - VD_Q_MAX];
 }
 __device__ __forceinline__ bool spill_has(const CellsDev &C, int b, int nt) {
-  const int*q = C.tq_spill + (long long)blockIdx.x * C.q_spill - VD_Q_MAX;
+  const int*q = C.tq_spill + (long long)blockIdx.x * (C.q_spill + VD_Q_MAX) - VD_Q_MAX;
   bool have = false;
   for (int e = VD_Q_MAX + vd_lane(); e < nt; e += 64) have = have || (q[e] == b);
   return have;
 }
 __device__ __forceinline__ void spill_put(const CellsDev &C, int i, int b) {
-  if (vd_lane() == 0) GL(C.tq_spill)[(long long)blockIdx.x * C.q_spill + i - VD_Q_MAX] = b;
+  if (vd_lane() == 0) GL(C.tq_spill)[(long long)blockIdx.x * (C.q_spill + VD_Q_MAX) + i - VD_Q_MAX] = b;
 }
 
 // Appends simplex b to the site's breadth-first queue unless it is there
@@ -929,35 +895,6 @@ __device__ __forceinline__ bool tq_push(WaveLds &S, const CellsDev &C, int &nt, 
   nt++;
   __syncthreads();
   return true;
-}
-
-// The lowest-index tetrahedron containing q (the whole wave scans the point's
-// location cell), or -1.
-__device__ int locate_wave(const DomainView &D, double qx, double qy, double qz) {
-  if (!D.lstart) return -1;
-  const double q[3] = {qx, qy, qz};
-  int cc[3];
-  for (int k = 0; k < 3; k++) cc[k] = cell_coord(q[k], GL(D.lgeom)[k], GL(D.lgeom)[6 + k], D.lg[k]);
-  const int c = cc[0] + D.lg[0] * (cc[1] + D.lg[1] * cc[2]);
-  int best = 0x7fffffff;
-  for (int t = GL(D.lstart)[c] + vd_lane(); t < GL(D.lstart)[c + 1]; t += 64) {
-    const int a = GL(D.litems)[t];
-    if (a < best && tet_contains(D, a, q)) best = a;
-  }
-  const int b = (int)wave_min((double)best);
-  return b == 0x7fffffff ? -1 : b;
-}
-
-// Is q in M?  One lane scans q's location cell (the tolerance of tet_contains
-// counts a point on the boundary as inside).
-__device__ bool in_domain(const DomainView &D, double qx, double qy, double qz) {
-  const double q[3] = {qx, qy, qz};
-  int cc[3];
-  for (int k = 0; k < 3; k++) cc[k] = cell_coord(q[k], GL(D.lgeom)[k], GL(D.lgeom)[6 + k], D.lg[k]);
-  const int c = cc[0] + D.lg[0] * (cc[1] + D.lg[1] * cc[2]);
-  for (int t = GL(D.lstart)[c]; t < GL(D.lstart)[c + 1]; t++)
-    if (tet_contains(D, GL(D.litems)[t], q)) return true;
-  return false;
 }
 
 // Do all nc corners of the polytope in S lie in M?  (Whole wave.)
@@ -1498,12 +1435,12 @@ __device__ void do_site(WaveLds &S, const GridView &G0, const DomainView &D0, co
 // convex domain).  Each is compiled in only for the instances that use it, so
 // the default instance carries none of them.
 template <bool MON, bool DENS, bool POW, bool CORNERS>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) site_kernel(GridView G, DomainView D, const CellsDev *__restrict__ Cp) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) site_kernel(GridView G, DomainView D, const CellsDev *__restrict__ Cp, int redo) {
   __shared__ WaveLds S;
   const CellsDev &C = *Cp;
   arena_init(S.ar);
   for (;;) {
-    const int si = queue_next(S.ar, C, G.n);
+    const int si = redo ? redo_next(C) : queue_next(S.ar, C, G.n);
     if (si < 0) break;
     // the site's own diagram (a batch) or the only one; one call site keeps
     // the per-site code inlined once
@@ -1521,6 +1458,7 @@ __global__ void queue_init(int *q, long long n, QueueStarts qs) {
   const int k = threadIdx.x;
   const long long q8 = (n + VD_QUEUES - 1) / VD_QUEUES;
   if (k < VD_QUEUES) q[k * VD_QSTRIDE] = (int)(qs.given ? qs.off[k] : (k * q8 < n ? k * q8 : n));
+  if (k == VD_QREDO) q[k * VD_QSTRIDE] = 0;
 }
 
 int resident_workgroups() {
@@ -1556,23 +1494,23 @@ void vd_launch_queue_init(int *queue, long long n, const long long *qoff, hipStr
 }
 
 void vd_launch_sites3d(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool monitor,
-                       bool density, bool power, bool corners, hipStream_t st) {
+                       bool density, bool power, bool corners, bool redo, hipStream_t st) {
   const dim3 grid(workgroups), block(64);
   if (power) {  // power diagrams: no density, interior split by the boundary diagram
-    if (monitor) hipLaunchKernelGGL((site_kernel<true, false, true, false>), grid, block, 0, st, G, D, Cdev);
-    else hipLaunchKernelGGL((site_kernel<false, false, true, false>), grid, block, 0, st, G, D, Cdev);
+    if (monitor) hipLaunchKernelGGL((site_kernel<true, false, true, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    else hipLaunchKernelGGL((site_kernel<false, false, true, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
   } else if (corners) {
-    if (monitor && density) hipLaunchKernelGGL((site_kernel<true, true, false, true>), grid, block, 0, st, G, D, Cdev);
-    else if (monitor) hipLaunchKernelGGL((site_kernel<true, false, false, true>), grid, block, 0, st, G, D, Cdev);
-    else if (density) hipLaunchKernelGGL((site_kernel<false, true, false, true>), grid, block, 0, st, G, D, Cdev);
-    else hipLaunchKernelGGL((site_kernel<false, false, false, true>), grid, block, 0, st, G, D, Cdev);
+    if (monitor && density) hipLaunchKernelGGL((site_kernel<true, true, false, true>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    else if (monitor) hipLaunchKernelGGL((site_kernel<true, false, false, true>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    else if (density) hipLaunchKernelGGL((site_kernel<false, true, false, true>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    else hipLaunchKernelGGL((site_kernel<false, false, false, true>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
   } else if (monitor && density) {
-    hipLaunchKernelGGL((site_kernel<true, true, false, false>), grid, block, 0, st, G, D, Cdev);
+    hipLaunchKernelGGL((site_kernel<true, true, false, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
   } else if (monitor) {
-    hipLaunchKernelGGL((site_kernel<true, false, false, false>), grid, block, 0, st, G, D, Cdev);
+    hipLaunchKernelGGL((site_kernel<true, false, false, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
   } else if (density) {
-    hipLaunchKernelGGL((site_kernel<false, true, false, false>), grid, block, 0, st, G, D, Cdev);
+    hipLaunchKernelGGL((site_kernel<false, true, false, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
   } else {
-    hipLaunchKernelGGL((site_kernel<false, false, false, false>), grid, block, 0, st, G, D, Cdev);
+    hipLaunchKernelGGL((site_kernel<false, false, false, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
   }
 }

@@ -79,6 +79,18 @@ __device__ __forceinline__ int queue_next(WaveArena &A, const CellsDev &C, long 
   return __builtin_amdgcn_readlane(r, 0);
 }
 
+// Next site of the list that the sweep kernel left (complete when this runs),
+// or -1.
+__device__ __forceinline__ int redo_next(const CellsDev &C) {
+  int r = -1;
+  if (vd_lane() == 0) {
+    const int n = (int)GL(C.cnt)[CNT_REDO];
+    const int v = __hip_atomic_fetch_add(GL(C.queue) + VD_QREDO * VD_QSTRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (v < n) r = GL(C.redo)[v];
+  }
+  return __builtin_amdgcn_readlane(r, 0);
+}
+
 // End of a persistent wave: mark the unused tail of its piece chunk and add
 // its statistics to the global counters.
 __device__ __forceinline__ void arena_close(WaveArena &A, const CellsDev &C) {

@@ -43,6 +43,7 @@ enum {
   CNT_NEWCORNERS,  // corners created by clips (one 3x3 solve each)
   CNT_WASTED,      // tested corners that a clip removed besides the one that triggered it
   CNT_FANTETS,     // fan tetrahedra integrated for piece moments
+  CNT_REDO,        // sites that the sweep kernel left to the general one (entries of redo)
   CNT_N
 };
 static_assert(CNT_N <= 64, "reset_counters clears the counters with one wave");
@@ -50,6 +51,7 @@ static_assert(CNT_N <= 64, "reset_counters clears the counters with one wave");
 // persistent kernels: one work queue per XCD (8 heads, one per 128-byte line)
 #define VD_QUEUES 8
 #define VD_QSTRIDE 32
+#define VD_QREDO VD_QUEUES  // one more head: the list of sites to redo
 
 struct vd_grid_s {
   int64_t n = 0, cap_n = 0;
@@ -221,7 +223,8 @@ struct CellsDev {
   // owning order[qoff[k] .. qoff[k+1])
   const int *order;
   long long qoff[VD_QUEUES + 1];
-  int *tq_spill;          // [workgroups * q_spill] overflow of the per-site simplex queue
+  int *tq_spill;          // [workgroups * (q_spill + VD_Q_MAX)] overflow of the per-site simplex queue
+  int *redo;              // [n] sites that the sweep kernel leaves to the general one
   int *nb_spill;          // [workgroups * nbs_cap] overflow of the per-site neighbour list
   int q_spill, nbs_cap;   // entries per workgroup of the two overflow buffers
   int *sq_spill;          // [workgroups * sq_cap] surface: overflow of a triangle's site list
@@ -252,7 +255,7 @@ struct vd_cells_s {
   hipEvent_t ev0 = nullptr, ev1 = nullptr, ev2 = nullptr;  // kernel timing (time_kernels)
   double carve_ms = -1.0, split_ms = -1.0;
   CellsDev *d_dev = nullptr;  // device copy of d (read by the piece kernel)
-  int64_t cap_spill = 0;      // workgroups covered by d.tq_spill / d.nb_spill / d.saved
+  int64_t cap_spill = 0, cap_gen = 0;  // workgroups covered by d.tq_spill, and by d.nb_spill / d.saved (general kernel)
   int q_spill_want = VD_Q_SPILL, nb_spill_want = VD_NB_SPILL;  // per-workgroup sizes (grow on retry)
   int64_t sq_spill_elems = 0;  // allocated entries of d.sq_spill
   int *order_buf = nullptr;     // d.order's storage, and the batch layout it was built for
@@ -402,7 +405,13 @@ void vd_launch_locate_sites(const GridView &G, const DomainView &D, int *seed, i
 int vd_sites3d_workgroups(long long n);
 void vd_launch_queue_init(int *queue, long long n, const long long *qoff, hipStream_t st);
 void vd_launch_sites3d(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool monitor,
-                       bool density, bool power, bool corners, hipStream_t st);
+                       bool density, bool power, bool corners, bool redo, hipStream_t st);
+// the default clip: workgroups of the sweep kernel, and its launch; the sites it
+// leaves in Cdev->redo are then taken by vd_launch_sites3d with redo = true
+int vd_sweep_workgroups(long long n);
+void vd_launch_sweep(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
+                     bool power, bool corners, bool bseeds, hipStream_t st);
+void vd_launch_void_pieces(const CellsDev *Cdev, hipStream_t st);  // between the two: drops half-done sites' pieces
 int vd_surface_workgroups(long long m);
 void vd_launch_surface(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
                        bool power, hipStream_t st);
