@@ -267,6 +267,7 @@ vd_status build_grid_impl(const double *sites, int64_t n, int nb, const int64_t 
       tmp = 0; if ((e = ensure(G->bbox_part, tmp, 6 * (int64_t)std::max(nb, 256))) != hipSuccess) goto herr;
       G->cap_nb = nb;
     }
+    G->surface = surface_area > 0;
     G->power = false;  // weights belong to one sorting of the sites
     GridShadow *sh;
     {
@@ -620,7 +621,6 @@ hipError_t alloc_cells(vd_cells c, int64_t n, const Caps &want) {
     t = 0; if ((e = ensure(d.pstart, t, n)) != hipSuccess) return e;
     t = 0; if ((e = ensure(d.nstart, t, n)) != hipSuccess) return e;
     t = 0; if ((e = ensure(d.seed, t, n)) != hipSuccess) return e;
-    t = 0; if ((e = ensure(d.redo, t, n)) != hipSuccess) return e;
     t = 0; if ((e = ensure(c->piece_off, t, n + 1)) != hipSuccess) return e;
     t = 0; if ((e = ensure(c->nbr_off, t, n + 1)) != hipSuccess) return e;
     t = 0; if ((e = ensure(c->scan_tmp, t, n / 1024 + 2)) != hipSuccess) return e;
@@ -891,8 +891,21 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     const int64_t items = dom->dim == 3 ? n : dom->m;  // sites, or triangles
     // the default search goes to the sweep kernel, the variants of the paper's
     // search, its counters and the per-simplex carve to the general one
-    const bool sweep = dom->dim == 3 && d.mode == 1 && (d.cache || g->power) && !d.improved && !d.straddle && !d.monitor;
-    const int wg = dom->dim == 2 ? vd_surface_workgroups(dom->m) : sweep ? vd_sweep_workgroups(n) : vd_sites3d_workgroups(n);
+    bool sweep = (dom->dim == 2 || d.mode == 1) && (d.cache || g->power) && !d.improved && !d.straddle && !d.monitor;
+    // sites on a surface, many to a triangle: the sweep's copy of 128 sites does
+    // not reach around the triangles and most would be done twice (200,000 sites
+    // on spheres of 1,280 / 5,120 / 20,480 triangles: 31.4 / 11.3 / 7.2 ms with
+    // the sweep and the searched kernel for its rest, 30.2 / 11.4 / 9.3 without)
+    if (dom->dim == 2 && g->surface && n > 64 * dom->m) sweep = false;
+    // (the list of what the sweep leaves, and for triangles the half-done ones)
+    const int64_t nredo = dom->dim == 3 ? n : 2 * dom->m;
+    if (sweep && c->cap_redo < nredo) {
+      if (opt.no_sync) sweep = false;  // (no allocation)
+      else HIP_TRY(ensure(d.redo, c->cap_redo, nredo));
+    }
+    d.voided = d.redo + dom->m;
+    const int wg = sweep ? (dom->dim == 2 ? vd_tri_workgroups(dom->m) : vd_sweep_workgroups(n))
+                         : (dom->dim == 2 ? vd_surface_workgroups(dom->m) : vd_sites3d_workgroups(n));
     // per-wave scratch of either kernel (a later no-sync clip may take the other)
     const int wgen = dom->dim == 3 ? vd_sites3d_workgroups(n) : 0;
     const int wgs = dom->dim == 3 ? std::max(vd_sweep_workgroups(n), wgen) : 0;
@@ -914,7 +927,7 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     if (dom->dim == 2) {
       // surface: a triangle's site list beyond its LDS part (none until a
       // triangle needs it; grown on retry)
-      const int64_t need = (int64_t)wg * c->sq_spill_want;
+      const int64_t need = (int64_t)vd_surface_workgroups(dom->m) * c->sq_spill_want;
       if (need > 0 && (c->sq_spill_elems < need || d.sq_cap != c->sq_spill_want)) {
         HIP_TRY(ensure(d.sq_spill, c->sq_spill_elems, need));
       }
@@ -1023,16 +1036,26 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     }
     if (dom->dim == 2) vd_launch_fill_int(d.pcount, n, 0, st);
     if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev0, st));
-    if (sweep) vd_launch_sweep(G, D, c->d_dev, wg, opt.use_density != 0, g->power, d.whole == 2, c->used_bseeds, st);
-    else if (dom->dim == 3) vd_launch_sites3d(G, D, c->d_dev, wg, opt.monitor != 0, opt.use_density != 0, g->power, d.whole == 2, false, st);
-    else vd_launch_surface(G, D, c->d_dev, wg, opt.use_density != 0, g->power, st);
+    if (dom->dim == 2 && sweep) vd_launch_tri(G, D, c->d_dev, wg, opt.use_density != 0, g->power, st);
+    else if (dom->dim == 2) vd_launch_surface(G, D, c->d_dev, wg, opt.use_density != 0, g->power, false, st);
+    else if (sweep) vd_launch_sweep(G, D, c->d_dev, wg, opt.use_density != 0, g->power, d.whole == 2, c->used_bseeds, st);
+    else vd_launch_sites3d(G, D, c->d_dev, wg, opt.monitor != 0, opt.use_density != 0, g->power, d.whole == 2, false, st);
     if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev1, st));
     HIP_TRY(hipGetLastError());
-    // the sites the sweep left (usually none; a no-sync clip cannot look)
-    const int wredo = std::min(wg, std::min(512, vd_sites3d_workgroups(n)));
+    // what the sweep left (usually nothing, and rarely much on solids; a no-sync
+    // clip cannot look)
+    auto rest = [&] {
+      if (dom->dim == 2) {
+        vd_launch_void_triangles(c->d_dev, st);
+        vd_launch_surface(G, D, c->d_dev, vd_surface_workgroups(dom->m), opt.use_density != 0, g->power, true, st);
+      } else {
+        vd_launch_void_pieces(c->d_dev, st);
+        vd_launch_sites3d(G, D, c->d_dev, std::min(wg, std::min(512, vd_sites3d_workgroups(n))), false,
+                          opt.use_density != 0, g->power, d.whole == 2, true, st);
+      }
+    };
     if (opt.no_sync) {
-      if (sweep) vd_launch_void_pieces(c->d_dev, st);
-      if (sweep) vd_launch_sites3d(G, D, c->d_dev, wredo, false, opt.use_density != 0, g->power, d.whole == 2, true, st);
+      if (sweep) rest();
       // stream-ordered only: finalize from the device counters, copy them to
       // pinned host memory, and check them in vd_cells_info
       c->pending = true;
@@ -1048,8 +1071,7 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     HIP_TRY(hipMemcpyAsync(c->host_cnt, d.cnt, sizeof(unsigned long long) * CNT_N, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (sweep && c->host_cnt[CNT_REDO]) {
-      vd_launch_void_pieces(c->d_dev, st);
-      vd_launch_sites3d(G, D, c->d_dev, wredo, false, opt.use_density != 0, g->power, d.whole == 2, true, st);
+      rest();
       if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev1, st));
       HIP_TRY(hipMemcpyAsync(c->host_cnt, d.cnt, sizeof(unsigned long long) * CNT_N, hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
@@ -1095,7 +1117,7 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
         hc[CNT_STAGES] == (1ull << VD_STAGE_TRIANGLE_SITES)) {
       // a triangle meets more cells than its wave's site list holds: grow the
       // overflow (within about 4 GB) and run again
-      const int64_t wmax = (int64_t)(1ll << 30) / std::max<int64_t>(wg, 1);
+      const int64_t wmax = (int64_t)(1ll << 30) / std::max<int64_t>(vd_surface_workgroups(dom->m), 1);
       const int64_t nw = std::min<int64_t>({std::max<int64_t>(4096, (int64_t)c->sq_spill_want * 4), n, wmax});
       if (nw > c->sq_spill_want) {
         c->sq_spill_want = (int)nw;

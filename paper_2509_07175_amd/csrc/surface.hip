@@ -704,16 +704,17 @@ __device__ void do_triangle(TriLds &S, const GridView &G, const DomainView &D, c
   __syncthreads();
 }
 
-// Persistent: every workgroup (one wave) takes triangles from the queues.
+// Persistent: every workgroup (one wave) takes triangles from the queues, or
+// (redo) from the list that the sweep kernel left.
 // Four waves per SIMD (128 VGPRs, a few spilled values): the polygon carve is
 // latency-bound, and the extra wave hides more of it than the spills cost.
 template <bool DENS, bool POW>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) surface_kernel(GridView G, DomainView D, const CellsDev *__restrict__ Cp) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) surface_kernel(GridView G, DomainView D, const CellsDev *__restrict__ Cp, int redo) {
   __shared__ TriLds S;
   const CellsDev &C = *Cp;
   arena_init(S.ar);
   for (;;) {
-    const int a = queue_next(S.ar, C, D.m);
+    const int a = redo ? redo_next(C) : queue_next(S.ar, C, D.m);
     if (a < 0) break;
     // the triangle's own diagram (a batch) or the only one
     const int b = D.nb > 1 ? diagram_of(D.simp_off, D.nb, a) : 0;
@@ -865,11 +866,11 @@ int vd_surface_workgroups(long long m) {
 }
 
 void vd_launch_surface(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
-                       bool power, hipStream_t st) {
+                       bool power, bool redo, hipStream_t st) {
   const dim3 grid((unsigned)workgroups), block(64);
-  if (power) hipLaunchKernelGGL((surface_kernel<false, true>), grid, block, 0, st, G, D, Cdev);
-  else if (density) hipLaunchKernelGGL((surface_kernel<true, false>), grid, block, 0, st, G, D, Cdev);
-  else hipLaunchKernelGGL((surface_kernel<false, false>), grid, block, 0, st, G, D, Cdev);
+  if (power) hipLaunchKernelGGL((surface_kernel<false, true>), grid, block, 0, st, G, D, Cdev, (int)redo);
+  else if (density) hipLaunchKernelGGL((surface_kernel<true, false>), grid, block, 0, st, G, D, Cdev, (int)redo);
+  else hipLaunchKernelGGL((surface_kernel<false, false>), grid, block, 0, st, G, D, Cdev, (int)redo);
 }
 
 void vd_launch_site_reduce(long long n, const long long *poff, const int *pid, const CellsDev *Cdev,

@@ -61,6 +61,17 @@ __device__ __forceinline__ long long arena_take(WaveArena &A, const CellsDev &C,
   return readlane_ll(o, 0);
 }
 
+// arena_take for k pieces at once: the slots that a chunk has left when it is
+// too short for them become unused ones.
+__device__ __forceinline__ long long arena_take_pieces(WaveArena &A, const CellsDev &C, long long k) {
+  const long long cur = readlane_ll(A.cur[AR_PIECE], 0), end = readlane_ll(A.end[AR_PIECE], 0);
+  if (cur + k > end) {
+    const long long p = cur + vd_lane();
+    if (p < end && p < C.cap_piece) GL(C.piece_site)[p] = -1;
+  }
+  return arena_take(A, C, AR_PIECE, k);
+}
+
 // Next work item in [0, n), or -1 when every queue is exhausted.
 __device__ __forceinline__ int queue_next(WaveArena &A, const CellsDev &C, long long n) {
   int r = -1;

@@ -43,7 +43,7 @@ enum {
   CNT_NEWCORNERS,  // corners created by clips (one 3x3 solve each)
   CNT_WASTED,      // tested corners that a clip removed besides the one that triggered it
   CNT_FANTETS,     // fan tetrahedra integrated for piece moments
-  CNT_REDO,        // sites that the sweep kernel left to the general one (entries of redo)
+  CNT_REDO,        // sites (triangles) that the sweep kernel left to the general one (entries of redo)
   CNT_N
 };
 static_assert(CNT_N <= 64, "reset_counters clears the counters with one wave");
@@ -66,6 +66,7 @@ struct vd_grid_s {
   double *sw = nullptr, *sh = nullptr, *eta = nullptr;
   int64_t cap_w = 0;
   bool power = false;
+  bool surface = false;  // the sites lie on a surface (the last build's surface_area > 0)
   int *perm = nullptr, *rank = nullptr, *cellid = nullptr, *fill = nullptr;
   int *cstart = nullptr, *ccount = nullptr, *scan_tmp = nullptr;
   // batch of nb diagrams (nb = 1: plain)
@@ -224,7 +225,8 @@ struct CellsDev {
   const int *order;
   long long qoff[VD_QUEUES + 1];
   int *tq_spill;          // [workgroups * (q_spill + VD_Q_MAX)] overflow of the per-site simplex queue
-  int *redo;              // [n] sites that the sweep kernel leaves to the general one
+  int *redo;              // sites [n] (triangles [m]) that the sweep kernel leaves to the general one
+  int *voided;            // [m] surface: the sweep kernel left this triangle half done
   int *nb_spill;          // [workgroups * nbs_cap] overflow of the per-site neighbour list
   int q_spill, nbs_cap;   // entries per workgroup of the two overflow buffers
   int *sq_spill;          // [workgroups * sq_cap] surface: overflow of a triangle's site list
@@ -241,7 +243,7 @@ struct vd_cells_s {
   bool pending = false;                    // a no-sync clip whose counters are not checked yet
   hipStream_t last_stream = nullptr;
   // capacities (host copy) and allocations
-  int64_t cap_n = 0;
+  int64_t cap_n = 0, cap_redo = 0;
   long long *piece_off = nullptr, *nbr_off = nullptr;  // CSR [n+1]
   int *piece_id = nullptr, *nbr = nullptr;             // CSR payloads
   int *fillc = nullptr;                                // per-site scatter counters
@@ -412,9 +414,15 @@ int vd_sweep_workgroups(long long n);
 void vd_launch_sweep(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
                      bool power, bool corners, bool bseeds, hipStream_t st);
 void vd_launch_void_pieces(const CellsDev *Cdev, hipStream_t st);  // between the two: drops half-done sites' pieces
+// the same for surfaces: sweep kernel, drop of half-done triangles' pieces, and
+// the searched kernel (of all triangles, or of those the sweep left)
+int vd_tri_workgroups(long long m);
+void vd_launch_tri(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
+                   bool power, hipStream_t st);
+void vd_launch_void_triangles(const CellsDev *Cdev, hipStream_t st);
 int vd_surface_workgroups(long long m);
 void vd_launch_surface(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
-                       bool power, hipStream_t st);
+                       bool power, bool redo, hipStream_t st);
 void vd_launch_site_nbrs(long long n, const long long *poff, const int *pid, const long long *noff, int *nbr,
                          long long cap, const CellsDev *Cdev, hipStream_t st);
 void vd_launch_site_reduce(long long n, const long long *poff, const int *pid, const CellsDev *Cdev,
