@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "vd_internal.h"
+#include "vd_pool.h"
 
 void vd_launch_domain_fill(vd_domain d, hipStream_t st);
 void vd_launch_domain_offsets(vd_domain d, int *flags, hipStream_t st);
@@ -56,12 +57,12 @@ template <typename T>
 hipError_t ensure(T *&p, int64_t &cap, int64_t need) {
   if (need <= cap && p) return hipSuccess;
   if (p) {
-    hipError_t e = hipFree(p);
+    hipError_t e = BlockPool::get().free_now(p);
     if (e != hipSuccess) return e;
     p = nullptr;
   }
   const int64_t n = std::max<int64_t>(need, 1);
-  hipError_t e = hipMalloc((void **)&p, sizeof(T) * (size_t)n);
+  hipError_t e = BlockPool::get().alloc((void **)&p, sizeof(T) * (size_t)n);
   if (e == hipSuccess) cap = n;
   else cap = 0;
   return e;
@@ -71,7 +72,7 @@ hipError_t ensure(T *&p, int64_t &cap, int64_t need) {
 template <typename T>
 hipError_t ensure_fixed(T *&p, int64_t n) {
   if (p) return hipSuccess;
-  return hipMalloc((void **)&p, sizeof(T) * (size_t)std::max<int64_t>(n, 1));
+  return BlockPool::get().alloc((void **)&p, sizeof(T) * (size_t)std::max<int64_t>(n, 1));
 }
 
 __global__ void reset_counters(unsigned long long *cnt) {
@@ -222,7 +223,10 @@ vd_status build_grid_impl(const double *sites, int64_t n, int nb, const int64_t 
   }
   if (coff[nb] > (int64_t)INT_MAX / 2) return fail(VD_ERR_INVALID_ARG, "%s: too many grid cells", who);
   vd_grid G = *out;
-  if (!G) G = new vd_grid_s();
+  if (!G) {
+    G = new vd_grid_s();
+    BlockPool::get().handle_made();
+  }
   auto fin = [&](vd_status r) {
     if (r != VD_OK && !*out) vd_grid_free(G);
     else *out = G;
@@ -327,13 +331,11 @@ vd_status vd_grid_set_weights(vd_grid G, const double *weights, void *stream) {
     HIP_TRY(ensure(G->sh, t, G->n));
     G->cap_w = t;
     HIP_TRY(ensure_fixed(G->eta, 1));
-    TmpBuffers tmp;
-    int *flags = nullptr;
-    HIP_TRY(tmp.get(flags, 1));
-    vd_launch_fill_int(flags, 1, 0, st);
-    vd_launch_grid_weights(G, weights, flags, st);
+    HIP_TRY(ensure_fixed(G->wflag, 1));
+    vd_launch_fill_int(G->wflag, 1, 0, st);
+    vd_launch_grid_weights(G, weights, G->wflag, st);
     int hf = 0;
-    HIP_TRY(hipMemcpyAsync(&hf, flags, sizeof hf, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(&hf, G->wflag, sizeof hf, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (hf) return fail(VD_ERR_INVALID_ARG, "vd_grid_set_weights: a weight is not finite");
   }
@@ -354,17 +356,17 @@ vd_status vd_grid_set_weights(vd_grid G, const double *weights, void *stream) {
 
 void vd_grid_free(vd_grid G) {
   if (!G) return;
-  hipFree(G->sw); hipFree(G->sh); hipFree(G->eta);
-  hipFree(G->geom); hipFree(G->bbox_part); hipFree(G->sx); hipFree(G->sy); hipFree(G->sz);
-  hipFree(G->delta); hipFree(G->perm); hipFree(G->rank); hipFree(G->cellid); hipFree(G->fill);
-  hipFree(G->cstart); hipFree(G->ccount); hipFree(G->scan_tmp);
-  hipFree(G->d_site_off); hipFree(G->d_cell_off); hipFree(G->d_dims); hipFree(G->diag); hipFree(G->d_user_box);
-  hipFree(G->d_views);
+  BlockPool::get().release({
+      G->sw, G->sh, G->eta, G->wflag, G->geom, G->bbox_part, G->sx, G->sy, G->sz, G->delta, G->perm, G->rank, G->cellid,
+      G->fill, G->cstart, G->ccount, G->scan_tmp, G->d_site_off, G->d_cell_off, G->d_dims, G->diag,
+      G->d_user_box, G->d_views
+  });
   {
     std::lock_guard<std::mutex> lk(g_shadow_mu);
     g_grid_shadow.erase(G);
   }
   delete G;
+  BlockPool::get().handle_gone();
 }
 
 // ---------------------------------------------------------------------------
@@ -392,6 +394,7 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
       return fail(VD_ERR_INVALID_ARG, "%s: diagram %d has an empty domain", who, b);
   hipStream_t st = as_stream(stream);
   vd_domain D = *out ? *out : new vd_domain_s();
+  if (!*out) BlockPool::get().handle_made();
   auto bail = [&](vd_status r) {
     if (!*out) vd_domain_free(D);
     return r;
@@ -597,6 +600,7 @@ void vd_domain_free(vd_domain D) {
   hipFree(D->litems); hipFree(D->lcount); hipFree(D->lfill); hipFree(D->scan_tmp);
   hipFree(D->d_simp_off); hipFree(D->d_vert_off); hipFree(D->d_loc_off); hipFree(D->d_lg); hipFree(D->d_views);
   delete D;
+  BlockPool::get().handle_gone();
 }
 
 // ---------------------------------------------------------------------------
@@ -630,7 +634,7 @@ hipError_t alloc_cells(vd_cells c, int64_t n, const Caps &want) {
   if ((e = ensure_fixed(d.cnt, CNT_N)) != hipSuccess) return e;
   if ((e = ensure_fixed(d.queue, (VD_QREDO + 1) * VD_QSTRIDE)) != hipSuccess) return e;
   if (!c->host_cnt) {
-    if ((e = hipHostMalloc((void **)&c->host_cnt, sizeof(unsigned long long) * CNT_N, hipHostMallocDefault)) !=
+    if ((e = BlockPool::get().alloc((void **)&c->host_cnt, sizeof(unsigned long long) * CNT_N, true)) !=
         hipSuccess)
       return e;
     std::memset(c->host_cnt, 0, sizeof(unsigned long long) * CNT_N);
@@ -835,6 +839,7 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
   }
   hipStream_t st = as_stream(stream);
   vd_cells c = *out ? *out : new vd_cells_s();
+  if (!*out) BlockPool::get().handle_made();
   const int64_t n = g->n;
   c->n = n;
   c->pending = false;
@@ -961,7 +966,7 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
       HIP_TRY(hipEventCreate(&c->ev1));
       HIP_TRY(hipEventCreate(&c->ev2));
     }
-    if (!c->d_dev) HIP_TRY(hipMalloc((void **)&c->d_dev, sizeof(CellsDev)));
+    HIP_TRY(ensure_fixed(c->d_dev, 1));
     if (std::memcmp(&c->d_shadow, &d, sizeof(CellsDev)) != 0) {
       c->d_shadow = d;
       HIP_TRY(hipMemcpyAsync(c->d_dev, &c->d_shadow, sizeof(CellsDev), hipMemcpyHostToDevice, st));
@@ -1151,23 +1156,20 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
 void vd_cells_free(vd_cells c) {
   if (!c) return;
   CellsDev &d = c->d;
-  hipFree(d.cnt); hipFree(d.mass); hipFree(d.mom); hipFree(d.energy); hipFree(d.pcount); hipFree(d.ncount);
-  hipFree(d.pstart); hipFree(d.nstart); hipFree(d.nbr_arena); hipFree(d.piece_site); hipFree(c->fillc);
-  hipFree(c->pid_tmp);
-  hipFree(d.piece_simplex); hipFree(d.piece_nface); hipFree(d.piece_nvert); hipFree(d.piece_fstart);
-  hipFree(d.piece_vstart); hipFree(d.piece_mass); hipFree(d.piece_mom); hipFree(d.piece_energy);
-  hipFree(d.face_label); hipFree(d.vert_xyz); hipFree(d.vert_label); hipFree(d.fint); hipFree(d.seed);
-  hipFree(c->piece_off); hipFree(c->nbr_off); hipFree(c->piece_id); hipFree(c->nbr); hipFree(c->scan_tmp);
+  BlockPool::get().release({
+      d.cnt, d.mass, d.mom, d.energy, d.pcount, d.ncount, d.pstart, d.nstart, d.nbr_arena, d.piece_site,
+      c->fillc, c->pid_tmp, d.piece_simplex, d.piece_nface, d.piece_nvert, d.piece_fstart, d.piece_vstart,
+      d.piece_mass, d.piece_mom, d.piece_energy, d.face_label, d.vert_xyz, d.vert_label, d.fint, d.seed,
+      c->piece_off, c->nbr_off, c->piece_id, c->nbr, c->scan_tmp, c->d_dev, d.queue, d.tq_spill, d.redo,
+      d.saved, c->outside, d.nb_spill, d.sq_spill, c->order_buf, d.fint_lab, d.piece_fint_start, d.piece_nfint,
+      c->wbuf, c->host_cnt
+  });
   if (c->ev0) hipEventDestroy(c->ev0);
   if (c->ev1) hipEventDestroy(c->ev1);
   if (c->ev2) hipEventDestroy(c->ev2);
-  hipFree(c->d_dev); hipFree(d.queue); hipFree(d.tq_spill); hipFree(d.redo); hipFree(d.saved);
-  hipFree(c->outside);
-  hipFree(d.nb_spill); hipFree(d.sq_spill); hipFree(c->order_buf);
   vd_cells_free(c->bcells);
-  if (c->host_cnt) hipHostFree(c->host_cnt);
-  hipFree(d.fint_lab); hipFree(d.piece_fint_start); hipFree(d.piece_nfint); hipFree(c->wbuf);
   delete c;
+  BlockPool::get().handle_gone();
 }
 
 vd_status vd_cells_info(vd_cells c, vd_cells_info_t *info) {

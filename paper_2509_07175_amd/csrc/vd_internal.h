@@ -64,6 +64,7 @@ struct vd_grid_s {
   // power diagram (vd_grid_set_weights): weights and lifted coordinates in
   // sorted order, eta = max w; cleared by every build
   double *sw = nullptr, *sh = nullptr, *eta = nullptr;
+  int *wflag = nullptr;       // a weight is not finite
   int64_t cap_w = 0;
   bool power = false;
   bool surface = false;  // the sites lie on a surface (the last build's surface_area > 0)
