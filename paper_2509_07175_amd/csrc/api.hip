@@ -858,13 +858,21 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
   // cut are on bisectors.  A quarter more for the ends of the waves' chunks.
   const double cn = (double)n, cm = (double)dom->m;
   const double pieces = dom->dim == 3 ? cn + cm + 6.0 * (std::cbrt(cn * cn * cm) + std::cbrt(cn * cm * cm)) : 0.0;
-  want.piece = std::max<int64_t>(c->d.cap_piece, std::max<int64_t>(8 * n + 3 * dom->m + 1024, (int64_t)(1.25 * pieces) + 1024));
-  want.nbr = std::max<int64_t>(c->d.cap_nbr, 20 * n + 1024);
+  // Few items to a wave: arenas of twice that, so that a wave takes half its share
+  // at a time (`div` below).  Every refill is an atomic on one line that all
+  // waves share, and in a clip this short they wait for it: 4,099 sites with
+  // gradients 1.92 -> 1.59 ms, 30,000 weighted ones 2.28 -> 1.88; nothing is
+  // gained from 60,000 sites on, where the arenas would be large.
+  const int64_t items = dom->dim == 3 ? n : dom->m;  // sites, or triangles
+  const bool few = items <= 8 * (int64_t)(dom->dim == 3 ? vd_sweep_workgroups(n) : vd_tri_workgroups(dom->m));
+  const int64_t room = few ? 2 : 1;
+  want.piece = std::max<int64_t>(c->d.cap_piece, room * std::max<int64_t>(8 * n + 3 * dom->m + 1024, (int64_t)(1.25 * pieces) + 1024));
+  want.nbr = std::max<int64_t>(c->d.cap_nbr, room * (20 * n + 1024));
   // surfaces always keep the edge flags of their pieces (the per-site pass reads them)
   const bool keep_faces = opt.emit_polytopes || dom->dim == 2;
   want.face = keep_faces ? std::max<int64_t>(c->d.cap_face, 10 * want.piece) : 0;
   want.vert = keep_faces ? std::max<int64_t>(c->d.cap_vert, 16 * want.piece) : 0;
-  want.fint = opt.want_grad ? std::max<int64_t>(c->d.cap_fint, std::max<int64_t>(4 * want.piece, (int64_t)(1.25 * (15.5 * cn + 4.2 * pieces)) + 1024)) : 0;
+  want.fint = opt.want_grad ? std::max<int64_t>(c->d.cap_fint, std::max<int64_t>(4 * want.piece, room * ((int64_t)(1.25 * (15.5 * cn + 4.2 * pieces)) + 1024))) : 0;
   if (opt.no_sync) {
     // no allocation: the arenas keep the sizes of the synchronous clip before
     want.piece = c->d.cap_piece; want.nbr = c->d.cap_nbr;
@@ -891,9 +899,6 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     d.density = opt.use_density ? 1 : 0;
     d.power = g->power ? 1 : 0;
     for (int k = 0; k < 10; k++) d.dens[k] = opt.use_density ? opt.density[k] : (k == 0 ? 1.0 : 0.0);
-    // persistent 3D kernel: each wave reserves output chunks of about 1/8 of an
-    // arena's share per wave, so unused chunk tails stay within 1/8 of it
-    const int64_t items = dom->dim == 3 ? n : dom->m;  // sites, or triangles
     // the default search goes to the sweep kernel, the variants of the paper's
     // search, its counters and the per-simplex carve to the general one
     bool sweep = (dom->dim == 2 || d.mode == 1) && (d.cache || g->power) && !d.improved && !d.straddle && !d.monitor;
@@ -938,11 +943,12 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
       }
       d.sq_cap = need > 0 ? c->sq_spill_want : 0;
     }
-    {
-      const int64_t caps[AR_N] = {d.cap_piece, d.cap_face, d.cap_vert, d.cap_nbr, d.cap_fint};
-      for (int r = 0; r < AR_N; r++)
-        d.chunk[r] = std::max<int64_t>(1, std::min<int64_t>(4096, caps[r] / (8 * (int64_t)wg)));
-    }
+    // each wave reserves output chunks of an eighth of an arena's share per wave
+    // (or half of it), so unused chunk tails stay within that part of the arena
+    if (!opt.no_sync) c->div = few && attempt == 0 ? 2 : 8;
+    const int64_t caps[AR_N] = {d.cap_piece, d.cap_face, d.cap_vert, d.cap_nbr, d.cap_fint};
+    for (int r = 0; r < AR_N; r++)
+      d.chunk[r] = std::max<int64_t>(1, std::min<int64_t>(4096, caps[r] / (c->div * (int64_t)wg)));
     hipLaunchKernelGGL(reset_counters, dim3(1), dim3(64), 0, st, d.cnt);
     // batches: the diagrams with the most tetrahedra per site first (below)
     d.order = nullptr;
@@ -1098,6 +1104,10 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     if (keep_faces && (int64_t)hc[CNT_VERTS] > d.cap_vert) { need.vert = up(hc[CNT_VERTS]); grow = true; }
     if (opt.want_grad && (int64_t)hc[CNT_FINT] > d.cap_fint) { need.fint = up(hc[CNT_FINT]); grow = true; }
     if (grow) { want = need; continue; }
+    // (a later no-sync clip cannot grow its arenas: it gets the small chunks
+    // unless the large ones left room)
+    for (int r = 0; r < AR_N; r++)
+      if ((int64_t)hc[r] + wg * d.chunk[r] / 2 > caps[r]) c->div = 8;
     if (dom->dim == 3 && hc[CNT_ERR_CAP] && !hc[CNT_ERR_DEG] && !hc[CNT_ERR_LOC]) {
       // a cell that meets more tetrahedra, or has more neighbours, than the
       // per-wave overflow buffers hold: grow them (within about 8 GB each) and

@@ -330,24 +330,26 @@ __device__ __forceinline__ bool do_tri(TriSweepLds &S, const GridView &G, const 
       before += g < grp ? k : 0;
       tot += k;
     }
-    const long long pidx = arena_take_pieces(S.ar, C, np) + __popcll(lead & low_mask(l & 48));
-    const long long fo = arena_take(S.ar, C, AR_FACE, tot) + before;
-    const long long vo = arena_take(S.ar, C, AR_VERT, tot) + before;
+    const int lab = ok && live ? S.lab[grp][gl] : -1;
+    const uint64_t seg = C.want_grad ? lanes(lab >= 0) : 0ull;  // bisector edges
+    arena_skip_pieces(S.ar, C, np);
+    const long long at = arena_take_all(S.ar, C, arena_counts(np, tot, tot, __popcll(seg)));
+    const long long pidx = readlane_ll(at, AR_PIECE) + __popcll(lead & low_mask(l & 48));
+    const long long fo = readlane_ll(at, AR_FACE) + before;
+    const long long vo = readlane_ll(at, AR_VERT) + before;
     written = true;
     // only records that fit are counted: the per-site CSR built from the
     // counts then stays inside the arenas (the clip reports the overflow)
     const bool fits_fv = fo + nv <= C.cap_face && vo + nv <= C.cap_vert;
     const bool fits_p = pidx < C.cap_piece;
-    const int lab = ok && live ? S.lab[grp][gl] : -1;
     const int orig = S.orig[me < 0 ? 0 : me];
     if (C.want_grad) {
       // segment moments of the bisector edges: a point of the edge moves in
       // the plane of T_a with speed (x - v_i).dv / (d s), s = |n - (n.N)N|
       // (n, N unit normals of the bisector and of T_a); 2-point Gauss-Legendre
       // is exact for the cubic integrand, 3 points with a density
-      const uint64_t all = lanes(lab >= 0);
-      const unsigned pos = row_of(all);
-      const long long base = arena_take(S.ar, C, AR_FINT, __popcll(all)) + __popcll(all & low_mask(l & 48));
+      const unsigned pos = row_of(seg);
+      const long long base = readlane_ll(at, AR_FINT) + __popcll(seg & low_mask(l & 48));
       const int npos = __popc(pos);
       const bool ffits = base + npos <= C.cap_fint;
       if (ok && gl == 0 && fits_p) {

@@ -380,8 +380,8 @@ __device__ __forceinline__ int ask_grid(SweepLds &S, const GridView &G, const Si
 // (centroid -27/48, points (3/5,1/5,1/5) 25/48); with a density every integrand
 // carries it and one degree-5 rule takes all twelve.
 template <bool DENS>
-__device__ __forceinline__ void face_moments(SweepLds &S, const Poly &Q, uint64_t fmask, const CellsDev &C,
-                                             const SiteCtx &X, long long pidx) {
+__device__ __forceinline__ void face_moments(SweepLds &S, const Poly &Q, const CellsDev &C,
+                                             const SiteCtx &X, long long pidx, uint64_t pos, long long base) {
   const int l = vd_lane();
   if (l < kP) S.F.pfirst[l] = 0x7fffffff;
   lds_order();
@@ -393,10 +393,8 @@ __device__ __forceinline__ void face_moments(SweepLds &S, const Poly &Q, uint64_
     atomicMin(&S.F.pfirst[p8(Q.cp, 2)], l);
   }
   lds_order();
-  const bool mine = in_mask(fmask) && S.plab[l < kP ? l : 0] >= 0;
-  const uint64_t pos = lanes(mine);
+  const bool mine = in_mask(pos);
   const int npos = __popcll(pos);
-  const long long base = arena_take(S.ar, C, AR_FINT, npos);
   const bool fits = base + npos <= C.cap_fint;
   if (l == 0 && pidx < C.cap_piece) {
     GL(C.piece_fint_start)[pidx] = base;
@@ -703,13 +701,10 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     if (l == 0) { S.acc[0] += pv; S.acc[1] += pmx; S.acc[2] += pmy; S.acc[3] += pmz; S.acc[4] += pe; }
     // ---- emit the piece ----
     const int nc = __popcll(Q.M), nface = __popcll(fmask);
-    const long long pidx = arena_take(S.ar, C, AR_PIECE, 1);
-    long long fo = 0, vo = 0;
-    if (C.emit) {
-      fo = arena_take(S.ar, C, AR_FACE, nface);
-      vo = arena_take(S.ar, C, AR_VERT, nc);
-    }
-    if (C.want_grad) face_moments<DENS>(S, Q, fmask, C, X, pidx);
+    const uint64_t bis = C.want_grad ? fmask & cellpos : 0ull;  // its bisector faces
+    const long long at = arena_take_all(S.ar, C, arena_counts(1, C.emit ? nface : 0, C.emit ? nc : 0, __popcll(bis)));
+    const long long pidx = readlane_ll(at, AR_PIECE), fo = readlane_ll(at, AR_FACE), vo = readlane_ll(at, AR_VERT);
+    if (C.want_grad) face_moments<DENS>(S, Q, C, X, pidx, bis, readlane_ll(at, AR_FINT));
     // a record that does not fit its arena is dropped and counted; the per-site
     // counts below only count what was written, so the CSR built from them
     // stays inside the arenas (the clip then reports VD_ERR_CAPACITY)

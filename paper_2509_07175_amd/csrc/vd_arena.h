@@ -19,57 +19,76 @@
 #pragma once
 #include "vd_internal.h"
 
+// A wave's totals for the counters of one kind, lane l of the close adding entry
+// l (one atomic instruction: counters of one line travel together).
 struct WaveArena {
   long long cur[AR_N], end[AR_N];
-  unsigned long long queries, cands, clips, gridq;
-  unsigned long long pieces, faces, verts, nbrs;  // records written (real counts)
-  unsigned long long dropped;                     // records that did not fit their arena
-  // work counters of the clips (lane 0 updates them in LDS, so they cost no
-  // registers across the carve)
-  unsigned long long rounds, classified, newc, wasted, fantets, lowmargin;
+  union {
+    unsigned long long stat[CNT_STATS];
+    struct {  // in the order of the counters from CNT_QUERIES on
+      unsigned long long queries, clips, cands, gridq;
+      unsigned long long pieces, faces, verts, nbrs;  // records written (real counts)
+      unsigned long long dropped;                     // records that did not fit their arena
+      // work counters of the clips (lane 0 updates them in LDS, so they cost no
+      // registers across the carve)
+      unsigned long long lowmargin, rounds, classified, newc, wasted, fantets;
+    };
+  };
   double minmargin;                               // smallest relative classification margin
   int qi;                                         // queues tried so far
 };
+static_assert(offsetof(WaveArena, fantets) - offsetof(WaveArena, queries) == 8 * (CNT_STATS - 1), "stat[] = the counters");
 
 __device__ __forceinline__ void arena_init(WaveArena &A) {
-  if (vd_lane() == 0) {
-    for (int r = 0; r < AR_N; r++) A.cur[r] = A.end[r] = 0;
-    A.queries = A.cands = A.clips = A.gridq = 0;
-    A.pieces = A.faces = A.verts = A.nbrs = 0;
-    A.dropped = 0;
-    A.rounds = A.classified = A.newc = A.wasted = A.fantets = A.lowmargin = 0;
+  const int l = vd_lane();
+  if (l < AR_N) A.cur[l] = A.end[l] = 0;
+  if (l < CNT_STATS) A.stat[l] = 0;
+  if (l == 0) {
     A.minmargin = 1.0;
     A.qi = 0;
   }
 }
 
-// k slots of arena r for this wave (k and r uniform); returns the first slot.
-// The returned range may reach past the arena's capacity: callers check.
-__device__ __forceinline__ long long arena_take(WaveArena &A, const CellsDev &C, int r, long long k) {
-  long long o = 0;
-  if (vd_lane() == 0) {
-    long long cur = A.cur[r];
-    if (cur + k > A.end[r]) {
-      const long long t = k > C.chunk[r] ? k : C.chunk[r];
-      cur = (long long)__hip_atomic_fetch_add(GL(C.cnt) + r, (unsigned long long)t, __ATOMIC_RELAXED,
+// k slots of each arena (lane r < AR_N: of arena r, 0 for none) for this wave;
+// returns the first slot in the same lanes.  The range may reach past the
+// arena's capacity: callers check.  All arenas that run short are refilled by
+// one atomic instruction: their counters share a line, and a small clip waits
+// for little else (thousands of waves, one site each).
+__device__ __forceinline__ long long arena_take_all(WaveArena &A, const CellsDev &C, long long k) {
+  const int l = vd_lane();
+  long long cur = 0;
+  if (l < AR_N) {
+    cur = A.cur[l];
+    if (k > 0 && cur + k > A.end[l]) {
+      const long long c = C.chunk[l], t = k > c ? k : c;
+      cur = (long long)__hip_atomic_fetch_add(GL(C.cnt) + l, (unsigned long long)t, __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_AGENT);
-      A.end[r] = cur + t;
+      A.end[l] = cur + t;
     }
-    A.cur[r] = cur + k;
-    o = cur;
+    A.cur[l] = cur + k;
   }
-  return readlane_ll(o, 0);
+  return cur;
 }
 
-// arena_take for k pieces at once: the slots that a chunk has left when it is
-// too short for them become unused ones.
-__device__ __forceinline__ long long arena_take_pieces(WaveArena &A, const CellsDev &C, long long k) {
+// (uniform counts -> lanes)
+__device__ __forceinline__ int arena_counts(int piece, int face, int vert, int fint) {
+  const int l = vd_lane();
+  return l == AR_PIECE ? piece : l == AR_FACE ? face : l == AR_VERT ? vert : l == AR_FINT ? fint : 0;
+}
+
+// k slots of arena r (k and r uniform); returns the first slot.
+__device__ __forceinline__ long long arena_take(WaveArena &A, const CellsDev &C, int r, long long k) {
+  return readlane_ll(arena_take_all(A, C, vd_lane() == r ? k : 0), r);
+}
+
+// The piece slots that a chunk has left when it is too short for the next k at
+// once become unused ones.
+__device__ __forceinline__ void arena_skip_pieces(WaveArena &A, const CellsDev &C, int k) {
   const long long cur = readlane_ll(A.cur[AR_PIECE], 0), end = readlane_ll(A.end[AR_PIECE], 0);
   if (cur + k > end) {
     const long long p = cur + vd_lane();
     if (p < end && p < C.cap_piece) GL(C.piece_site)[p] = -1;
   }
-  return arena_take(A, C, AR_PIECE, k);
 }
 
 // Next work item in [0, n), or -1 when every queue is exhausted.
@@ -106,26 +125,13 @@ __device__ __forceinline__ int redo_next(const CellsDev &C) {
 // its statistics to the global counters.
 __device__ __forceinline__ void arena_close(WaveArena &A, const CellsDev &C) {
   const int l = vd_lane();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (written by other lanes)
+  __builtin_amdgcn_wave_barrier();
   const long long a = A.cur[AR_PIECE], b = A.end[AR_PIECE] < C.cap_piece ? A.end[AR_PIECE] : C.cap_piece;
   for (long long p = a + l; p < b; p += 64) GL(C.piece_site)[p] = -1;
-  if (l == 0) {
-    atomicAdd(&C.cnt[CNT_QUERIES], A.queries);
-    atomicAdd(&C.cnt[CNT_CANDS], A.cands);
-    atomicAdd(&C.cnt[CNT_CLIPS], A.clips);
-    atomicAdd(&C.cnt[CNT_GRIDQ], A.gridq);
-    atomicAdd(&C.cnt[CNT_REAL_PIECES], A.pieces);
-    atomicAdd(&C.cnt[CNT_REAL_FACES], A.faces);
-    atomicAdd(&C.cnt[CNT_REAL_VERTS], A.verts);
-    atomicAdd(&C.cnt[CNT_REAL_NBRS], A.nbrs);
-    if (A.dropped) atomicAdd(&C.cnt[CNT_OVERFLOW], A.dropped);
-    atomicAdd(&C.cnt[CNT_ROUNDS], A.rounds);
-    atomicAdd(&C.cnt[CNT_CLASSIFIED], A.classified);
-    atomicAdd(&C.cnt[CNT_NEWCORNERS], A.newc);
-    atomicAdd(&C.cnt[CNT_WASTED], A.wasted);
-    atomicAdd(&C.cnt[CNT_FANTETS], A.fantets);
-    if (A.lowmargin) atomicAdd(&C.cnt[CNT_LOWMARGIN], A.lowmargin);
+  if (l < CNT_STATS && A.stat[l]) atomicAdd(&C.cnt[CNT_QUERIES + l], A.stat[l]);
+  if (l == 0 && A.minmargin < 1.0)
     atomicMin(&C.cnt[CNT_MINMARGIN], (unsigned long long)__double_as_longlong(A.minmargin));
-  }
 }
 
 // Adds v to a work counter of the wave's LDS totals: an LDS atomic from lane 0

@@ -32,19 +32,22 @@ enum { AR_PIECE = 0, AR_FACE, AR_VERT, AR_NBR, AR_FINT, AR_N };
 // high-water marks (index = arena id), CNT_REAL_* the records actually written
 enum {
   CNT_PIECES = AR_PIECE, CNT_FACES = AR_FACE, CNT_VERTS = AR_VERT, CNT_NBRS = AR_NBR, CNT_FINT = AR_FINT,
-  CNT_QUERIES = AR_N, CNT_CLIPS, CNT_CANDS, CNT_ERR_CAP, CNT_ERR_DEG, CNT_ERR_LOC, CNT_BAD_SITE,
-  CNT_REAL_PIECES, CNT_REAL_FACES, CNT_REAL_VERTS, CNT_REAL_NBRS, CNT_STAGES, CNT_GRIDQ,
+  // (a wave's totals: WaveArena holds them in this order)
+  CNT_QUERIES = AR_N, CNT_CLIPS, CNT_CANDS, CNT_GRIDQ,
+  CNT_REAL_PIECES, CNT_REAL_FACES, CNT_REAL_VERTS, CNT_REAL_NBRS,
   CNT_OVERFLOW,    // records dropped because an arena was full (pieces, per-piece faces / vertices /
                    // face moments, per-site neighbour lists)
   CNT_LOWMARGIN,   // corner classifications whose relative margin was below 1e-12
-  CNT_MINMARGIN,   // bits of the smallest relative margin seen (a non-negative double)
   CNT_ROUNDS,      // nearest-site query rounds (a batch of up to four tests is one round)
   CNT_CLASSIFIED,  // corners classified against a clipping plane
   CNT_NEWCORNERS,  // corners created by clips (one 3x3 solve each)
   CNT_WASTED,      // tested corners that a clip removed besides the one that triggered it
   CNT_FANTETS,     // fan tetrahedra integrated for piece moments
+  CNT_MINMARGIN,   // bits of the smallest relative margin seen (a non-negative double)
+  CNT_ERR_CAP, CNT_ERR_DEG, CNT_ERR_LOC, CNT_BAD_SITE, CNT_STAGES,
   CNT_REDO,        // sites (triangles) that the sweep kernel left to the general one (entries of redo)
-  CNT_N
+  CNT_N,
+  CNT_STATS = CNT_FANTETS - CNT_QUERIES + 1
 };
 static_assert(CNT_N <= 64, "reset_counters clears the counters with one wave");
 
@@ -245,6 +248,7 @@ struct vd_cells_s {
   hipStream_t last_stream = nullptr;
   // capacities (host copy) and allocations
   int64_t cap_n = 0, cap_redo = 0;
+  int div = 8;  // a wave's chunk is this part of its share of an arena
   long long *piece_off = nullptr, *nbr_off = nullptr;  // CSR [n+1]
   int *piece_id = nullptr, *nbr = nullptr;             // CSR payloads
   int *fillc = nullptr;                                // per-site scatter counters
