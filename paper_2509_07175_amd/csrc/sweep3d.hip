@@ -71,9 +71,10 @@ struct __align__(16) SweepLds {
       unsigned long long bits[kBatch][kNB];  // the candidates of each bucket
     } B;
     struct {
-      double y[3][64];       // corners of a piece
-      double foot[kP][3];    // foot of each face's plane seen from the piece's first corner
-      int cp[64], nb[64], pfirst[kP];  // topology and lowest corner of each plane (face moments)
+      double y[64][4];       // corners of a piece
+      unsigned tri[128];     // triangles of its faces: three corners
+      int pfirst[kP];        // lowest corner of each plane
+      int cp[64], nb[64];    // topology (face moments)
     } F;
   };
   double step, keep;         // bucket width (squared distance); radius within which every block site is held
@@ -371,6 +372,58 @@ __device__ __forceinline__ int ask_grid(SweepLds &S, const GridView &G, const Si
   return 0;
 }
 
+// planes_in_use for a piece, and the lowest corner of each plane to F.pfirst
+__device__ __forceinline__ uint64_t faces_of(SweepLds &S, const Poly &Q) {
+  const int l = vd_lane();
+  if (l < kP) S.F.pfirst[l] = 64;
+  lds_order();
+  if (in_mask(Q.M)) {
+    atomicMin(&S.F.pfirst[p8(Q.cp, 0)], l);
+    atomicMin(&S.F.pfirst[p8(Q.cp, 1)], l);
+    atomicMin(&S.F.pfirst[p8(Q.cp, 2)], l);
+  }
+  lds_order();
+  return lanes(l < kP && S.F.pfirst[l < kP ? l : 0] < 64);
+}
+
+// Lists the triangles (lowest corner, corner, next corner) of the faces that do
+// not hold corner `first`, the lowest one; returns their number (124 at most).
+__device__ __forceinline__ int list_triangles(SweepLds &S, const Poly &Q, int first) {
+  const int l = vd_lane();
+  int T = 0;
+#pragma unroll
+  for (int e = 0; e < 3; e++) {
+    // plane e of the corner continues around its face to the corner across edge e + 2
+    const int nx = across(Q, e == 0 ? 2 : e - 1), s = S.F.pfirst[p8(Q.cp, e)];
+    const uint64_t act = lanes((s != first) & (s != l) & (s != nx)) & Q.M;
+    if (in_mask(act)) S.F.tri[T + mbcnt64(act)] = (unsigned)(s | l << 8 | nx << 16);
+    T += __popcll(act);
+  }
+  lds_order();
+  return T;
+}
+
+// Sums over the wave by the matrix cores: a product with ones adds the four
+// lanes 16 apart, a second one the four of a quad.  The four blocks of lanes
+// that are left (bits 2 and 3) are added for four sums at once, sum r in the
+// lanes of r = l & 3: 8 MFMA and 12 VALU instructions where the butterfly of
+// four sums takes 92.
+__device__ __forceinline__ double block_sum(double v) {
+  const double rows = __builtin_amdgcn_mfma_f64_4x4x4f64(v, 1.0, 0.0, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, rows, 0.0, 0, 0, 0);
+}
+__device__ __forceinline__ double blocks_sum(double v) {
+  v += perm_d<0x128>(v);  // row_ror:8
+  v += perm_d<0x124>(v);  // row_ror:4
+  return v;
+}
+__device__ __forceinline__ void wave_sum4(double &a, double &b, double &c, double &d) {
+  const int r = vd_lane() & 3;
+  const double A = block_sum(a), B = block_sum(b), C = block_sum(c), E = block_sum(d);
+  const double t = blocks_sum(r == 0 ? A : r == 1 ? B : r == 2 ? C : E);
+  a = readlane_d(t, 0); b = readlane_d(t, 1); c = readlane_d(t, 2); d = readlane_d(t, 3);
+}
+
 // Face moments of the bisector faces of the piece, for the adjoint: for face x
 // on B_ik, I0 = int y dA/d, I1 = int y y^T dA/d, I2 = int |y|^2 y dA/d with
 // y = x - v_i and d = |v_k - v_i|.  Lane x walks around face x from its lowest
@@ -383,14 +436,10 @@ template <bool DENS>
 __device__ __forceinline__ void face_moments(SweepLds &S, const Poly &Q, const CellsDev &C,
                                              const SiteCtx &X, long long pidx, uint64_t pos, long long base) {
   const int l = vd_lane();
-  if (l < kP) S.F.pfirst[l] = 0x7fffffff;
-  lds_order();
   if (in_mask(Q.M)) {
     S.F.cp[l] = Q.cp;
     S.F.nb[l] = Q.nb;
-    atomicMin(&S.F.pfirst[p8(Q.cp, 0)], l);
-    atomicMin(&S.F.pfirst[p8(Q.cp, 1)], l);
-    atomicMin(&S.F.pfirst[p8(Q.cp, 2)], l);
+    S.F.y[l][0] = Q.y0; S.F.y[l][1] = Q.y1; S.F.y[l][2] = Q.y2;
   }
   lds_order();
   const bool mine = in_mask(pos);
@@ -413,13 +462,13 @@ __device__ __forceinline__ void face_moments(SweepLds &S, const Poly &Q, const C
     for (int k = 0; k < 12; k++) I[k] = 0.0;
     const int start = S.F.pfirst[x];
     int T = start;
-    double a0 = S.F.y[0][T], a1 = S.F.y[1][T], a2 = S.F.y[2][T];
+    double a0 = S.F.y[T][0], a1 = S.F.y[T][1], a2 = S.F.y[T][2];
 #pragma unroll 1
     for (int s = 0; s < 64; s++) {
       const int pl = S.F.cp[T];
       const int e = p8(pl, 0) == x ? 0 : (p8(pl, 1) == x ? 1 : 2);
       const int nx = ~p8(S.F.nb[T], e == 0 ? 2 : e - 1) & 63;
-      const double b0 = S.F.y[0][nx], b1 = S.F.y[1][nx], b2 = S.F.y[2][nx];
+      const double b0 = S.F.y[nx][0], b1 = S.F.y[nx][1], b2 = S.F.y[nx][2];
       const double u0 = a0 - r0, u1 = a1 - r1, u2 = a2 - r2, w0 = b0 - r0, w1 = b1 - r1, w2 = b2 - r2;
       const double A = 0.5 * ((u1 * w2 - u2 * w1) * h0 + (u2 * w0 - u0 * w2) * h1 + (u0 * w1 - u1 * w0) * h2);
       if (DENS) {
@@ -643,61 +692,63 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
         if (~all) { head--; continue; }
       }
     }
-    // ---- moments of the piece: a fan of tetrahedra (o, foot of a face's plane
-    // seen from o, corner, next corner) with the apex o at a corner of the
-    // piece, so that the volume's rounding error scales with the piece and not
-    // with its distance to v_i ----
-    const uint64_t fmask = planes_in_use(S, Q);
+    // ---- moments of the piece: tetrahedra of a corner o and the triangles of
+    // the faces that do not hold it (about 40, one to a lane), in coordinates
+    // relative to o, so that the rounding error scales with the piece and not
+    // with its distance to v_i.  With a density, four Lloyd steps of 60,000
+    // sites: 15.1 ms with 15 points in three tetrahedra per corner (the planes'
+    // feet and three edges, 26 lanes at work), 8.7 ms here; without one the
+    // chain of LDS round trips is what it costs either way (25.7 ms of 26.3 on
+    // the 1M clustered workload) ----
+    const uint64_t fmask = faces_of(S, Q);
     const bool live = in_mask(Q.M);
     const int first = __ffsll((unsigned long long)Q.M) - 1;
     const double o0 = readlane_d(Q.y0, first), o1 = readlane_d(Q.y1, first), o2 = readlane_d(Q.y2, first);
-    if (live) { S.F.y[0][l] = Q.y0; S.F.y[1][l] = Q.y1; S.F.y[2][l] = Q.y2; }
-    if (in_mask(fmask)) {
-      const double n0 = S.pn[l][0], n1 = S.pn[l][1], n2 = S.pn[l][2];
-      const double f = (S.pn[l][3] - (n0 * o0 + n1 * o1 + n2 * o2)) / (n0 * n0 + n1 * n1 + n2 * n2);
-      S.F.foot[l][0] = n0 * f; S.F.foot[l][1] = n1 * f; S.F.foot[l][2] = n2 * f;
-    }
-    lds_order();
+    if (live) { S.F.y[l][0] = Q.y0 - o0; S.F.y[l][1] = Q.y1 - o1; S.F.y[l][2] = Q.y2 - o2; }
+    const int T = list_triangles(S, Q, first);
     double pv = 0, pmx = 0, pmy = 0, pmz = 0, pe = 0;
-    double dm = 0, dmx = 0, dmy = 0, dmz = 0, de = 0;  // density-weighted (DENS)
-    if (live) {
-      const double oo = o0 * o0 + o1 * o1 + o2 * o2;
-      const double y0 = Q.y0 - o0, y1 = Q.y1 - o1, y2 = Q.y2 - o2;
-      const double YY = Q.y0 * Q.y0 + Q.y1 * Q.y1 + Q.y2 * Q.y2;
+    double dm = 0;  // (DENS: the moments are weighted, pv is the volume)
+    ConeDensity cd;
+    if (DENS) cd = cone_density(C.dens, X.vx + o0, X.vy + o1, X.vz + o2);
 #pragma unroll 1
-      for (int e = 0; e < 3; e++) {
-        // plane e of the corner continues around its face to the corner across edge e + 2
-        const int x = p8(Q.cp, e), nx = across(Q, e == 0 ? 2 : e - 1);
-        const double r0 = S.F.foot[x][0], r1 = S.F.foot[x][1], r2 = S.F.foot[x][2];
-        const double Z0 = S.F.y[0][nx], Z1 = S.F.y[1][nx], Z2 = S.F.y[2][nx];
-        const double z0 = Z0 - o0, z1 = Z1 - o1, z2 = Z2 - o2;
-        const double det = r0 * (y1 * z2 - y2 * z1) - r1 * (y0 * z2 - y2 * z0) + r2 * (y0 * z1 - y1 * z0);
-        const double vol = det * (1.0 / 6.0);
-        // the tetrahedron's corners relative to v_i: o, o + r, Y, Z
-        const double R0 = o0 + r0, R1 = o1 + r1, R2 = o2 + r2;
-        const double s0 = o0 + R0 + Q.y0 + Z0, s1 = o1 + R1 + Q.y1 + Z1, s2 = o2 + R2 + Q.y2 + Z2;
-        pv += vol;
-        pmx += vol * s0 * 0.25; pmy += vol * s1 * 0.25; pmz += vol * s2 * 0.25;
-        pe += vol * (1.0 / 20.0) *
-              (oo + R0 * R0 + R1 * R1 + R2 * R2 + YY + Z0 * Z0 + Z1 * Z1 + Z2 * Z2 + s0 * s0 + s1 * s1 + s2 * s2);
+    for (int t0 = 0; t0 < T; t0 += 64) {
+      if (t0 + l < T) {
+        const unsigned tri = S.F.tri[t0 + l];
+        const double *P = S.F.y[tri & 255], *Y = S.F.y[(tri >> 8) & 255], *Z = S.F.y[tri >> 16];
+        const double p[3] = {P[0], P[1], P[2]}, y[3] = {Y[0], Y[1], Y[2]}, z[3] = {Z[0], Z[1], Z[2]};
+        // 6 vol of (0, p, y, z)
+        const double det = p[0] * (y[1] * z[2] - y[2] * z[1]) - p[1] * (y[0] * z[2] - y[2] * z[0]) +
+                           p[2] * (y[0] * z[1] - y[1] * z[0]);
+        pv += det;
         if (DENS) {
-          const double V0[3] = {o0, o1, o2}, V1[3] = {R0, R1, R2}, V2[3] = {Q.y0, Q.y1, Q.y2}, V3[3] = {Z0, Z1, Z2};
-          tet_density_moments(C.dens, X.vx, X.vy, X.vz, V0, V1, V2, V3, vol, dm, dmx, dmy, dmz, de);
+          cone_density_moments(cd, p, y, z, det, dm, pmx, pmy, pmz, pe);
+        } else {
+          const double s0 = p[0] + y[0] + z[0], s1 = p[1] + y[1] + z[1], s2 = p[2] + y[2] + z[2];
+          pmx += det * s0; pmy += det * s1; pmz += det * s2;
+          pe += det * (p[0] * p[0] + p[1] * p[1] + p[2] * p[2] + y[0] * y[0] + y[1] * y[1] + y[2] * y[2] +
+                       z[0] * z[0] + z[1] * z[1] + z[2] * z[2] + s0 * s0 + s1 * s1 + s2 * s2);
         }
       }
     }
-    pv = wave_sum(pv);
+    if (DENS) {
+      pv = readlane_d(blocks_sum(block_sum(pv)), 0);
+    } else {
+      dm = pv;
+    }
+    wave_sum4(dm, pmx, pmy, pmz);
+    pe = readlane_d(blocks_sum(block_sum(pe)), 0);
+    if (!DENS) pv = dm;
     // a piece exists when its volume is positive; with a density its moments
     // are the weighted ones
     if (!(pv > 0.0)) {
       if (whole) break;
       continue;
     }
-    if (DENS) {
-      pv = wave_sum(dm); pmx = wave_sum(dmx); pmy = wave_sum(dmy); pmz = wave_sum(dmz); pe = wave_sum(de);
-    } else {
-      pmx = wave_sum(pmx); pmy = wave_sum(pmy); pmz = wave_sum(pmz); pe = wave_sum(pe);
-    }
+    // from o to v_i
+    pv = dm * (1.0 / 6.0);
+    pmx *= DENS ? 1.0 / 6.0 : 1.0 / 24.0; pmy *= DENS ? 1.0 / 6.0 : 1.0 / 24.0; pmz *= DENS ? 1.0 / 6.0 : 1.0 / 24.0;
+    pe = pe * (DENS ? 1.0 / 6.0 : 1.0 / 120.0) + 2.0 * (o0 * pmx + o1 * pmy + o2 * pmz) + (o0 * o0 + o1 * o1 + o2 * o2) * pv;
+    pmx += o0 * pv; pmy += o1 * pv; pmz += o2 * pv;
     if (l == 0) { S.acc[0] += pv; S.acc[1] += pmx; S.acc[2] += pmy; S.acc[3] += pmz; S.acc[4] += pe; }
     // ---- emit the piece ----
     const int nc = __popcll(Q.M), nface = __popcll(fmask);

@@ -341,6 +341,53 @@ __device__ __forceinline__ void tet_density_moments(const double *c, double vx, 
   mass += sc * am; m0 += sc * a0; m1 += sc * a1; m2 += sc * a2; e += sc * ae;
 }
 
+// The density about a point q: rho(q + z) = r + g.z + z^T h z.
+struct ConeDensity {
+  double r, g0, g1, g2, h[6];  // h: xx, xy, xz, yy, yz, zz
+};
+__device__ __forceinline__ ConeDensity cone_density(const double *c, double x, double y, double z) {
+  ConeDensity d;
+  d.r = density_at(c, x, y, z);
+  d.g0 = c[1] + 2.0 * c[4] * x + c[5] * y + c[6] * z;
+  d.g1 = c[2] + c[5] * x + 2.0 * c[7] * y + c[8] * z;
+  d.g2 = c[3] + c[6] * x + c[8] * y + 2.0 * c[9] * z;
+  for (int k = 0; k < 6; k++) d.h[k] = c[4 + k];
+  return d;
+}
+
+// Six times the density-weighted moments of the tetrahedron (0, P, Y, Z) about
+// the point of `d` (det = 6 vol): mass += int rho, m += int rho z,
+// e += int rho |z|^2.  A part of degree k of an integrand is homogeneous, so its
+// mean over the tetrahedron is 3 / (k + 3) of its mean over the triangle
+// opposite the origin, and those means come from the rule of Dunavant of degree 4
+// with 6 points (all integrands have degree 4 at most): about 33 operations a
+// point, where the rule of tet_density_moments takes 27 at 15 points.
+__device__ __forceinline__ void cone_density_moments(const ConeDensity &d, const double *P, const double *Y,
+                                                     const double *Z, double det, double &mass, double &m0, double &m1,
+                                                     double &m2, double &e) {
+  // barycentric (t, t, 1 - 2t) in all orders
+  constexpr double tA = 0.44594849091596488632, wA = 0.22338158967801146570;
+  constexpr double tB = 0.09157621350977074346, wB = 0.10995174365532186764;
+  const double S0 = P[0] + Y[0] + Z[0], S1 = P[1] + Y[1] + Z[1], S2 = P[2] + Y[2] + Z[2];
+  double am = 0, a0 = 0, a1 = 0, a2 = 0, ae = 0;
+#pragma unroll
+  for (int c = 0; c < 2; c++) {
+    const double t = c ? tB : tA, u = 1.0 - 3.0 * t, w = c ? wB : wA;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      const double *V = k == 0 ? P : (k == 1 ? Y : Z);
+      const double z0 = t * S0 + u * V[0], z1 = t * S1 + u * V[1], z2 = t * S2 + u * V[2];
+      const double L = d.g0 * z0 + d.g1 * z1 + d.g2 * z2;
+      const double B = z0 * (d.h[0] * z0 + d.h[1] * z1 + d.h[2] * z2) + z1 * (d.h[3] * z1 + d.h[4] * z2) + d.h[5] * z2 * z2;
+      const double b = w * (0.75 * d.r + 0.6 * L + 0.5 * B);
+      am += w * (d.r + 0.75 * L + 0.6 * B);
+      a0 += b * z0; a1 += b * z1; a2 += b * z2;
+      ae += w * (0.6 * d.r + 0.5 * L + 3.0 / 7.0 * B) * (z0 * z0 + z1 * z1 + z2 * z2);
+    }
+  }
+  mass += det * am; m0 += det * a0; m1 += det * a1; m2 += det * a2; e += det * ae;
+}
+
 // Density-weighted integrals over a triangle (A0, A1, A2 relative to v,
 // area `area`) of y, y y^T and |y|^2 y (the adjoint's face moments before the
 // division by |v_k - v|): rule of Grundmann and Moeller of degree 5
