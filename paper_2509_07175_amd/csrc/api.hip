@@ -1047,9 +1047,10 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     }
     if (dom->dim == 2) vd_launch_fill_int(d.pcount, n, 0, st);
     if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev0, st));
-    if (dom->dim == 2 && sweep) vd_launch_tri(G, D, c->d_dev, wg, opt.use_density != 0, g->power, st);
+    if (dom->dim == 2 && sweep) vd_launch_tri(G, D, c->d_dev, wg, opt.use_density != 0, g->power, opt.want_grad != 0, st);
     else if (dom->dim == 2) vd_launch_surface(G, D, c->d_dev, wg, opt.use_density != 0, g->power, false, st);
-    else if (sweep) vd_launch_sweep(G, D, c->d_dev, wg, opt.use_density != 0, g->power, d.whole == 2, c->used_bseeds, st);
+    else if (sweep) vd_launch_sweep(G, D, c->d_dev, wg, opt.use_density != 0, g->power, d.whole == 2, c->used_bseeds,
+                                opt.want_grad != 0, st);
     else vd_launch_sites3d(G, D, c->d_dev, wg, opt.monitor != 0, opt.use_density != 0, g->power, d.whole == 2, false, st);
     if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev1, st));
     HIP_TRY(hipGetLastError());

@@ -89,7 +89,7 @@ __device__ __forceinline__ unsigned row_of(uint64_t m) { return (unsigned)(m >> 
 
 // One triangle; false: it has to go to the general kernel (`written` tells
 // whether pieces of it are in the arenas).
-template <bool DENS, bool POW>
+template <bool DENS, bool POW, bool GRAD>
 __device__ __forceinline__ bool do_tri(TriSweepLds &S, const GridView &G, const DomainView &D, const CellsDev &C, int a,
                                        bool &written) {
   const int l = vd_lane(), gl = l & 15, grp = l >> 4;
@@ -331,7 +331,7 @@ __device__ __forceinline__ bool do_tri(TriSweepLds &S, const GridView &G, const 
       tot += k;
     }
     const int lab = ok && live ? S.lab[grp][gl] : -1;
-    const uint64_t seg = C.want_grad ? lanes(lab >= 0) : 0ull;  // bisector edges
+    const uint64_t seg = GRAD ? lanes(lab >= 0) : 0ull;  // bisector edges
     arena_skip_pieces(S.ar, C, np);
     const long long at = arena_take_all(S.ar, C, arena_counts(np, tot, tot, __popcll(seg)));
     const long long pidx = readlane_ll(at, AR_PIECE) + __popcll(lead & low_mask(l & 48));
@@ -343,7 +343,7 @@ __device__ __forceinline__ bool do_tri(TriSweepLds &S, const GridView &G, const 
     const bool fits_fv = fo + nv <= C.cap_face && vo + nv <= C.cap_vert;
     const bool fits_p = pidx < C.cap_piece;
     const int orig = S.orig[me < 0 ? 0 : me];
-    if (C.want_grad) {
+    if (GRAD) {
       // segment moments of the bisector edges: a point of the edge moves in
       // the plane of T_a with speed (x - v_i).dv / (d s), s = |n - (n.N)N|
       // (n, N unit normals of the bisector and of T_a); 2-point Gauss-Legendre
@@ -448,7 +448,7 @@ __device__ __forceinline__ bool do_tri(TriSweepLds &S, const GridView &G, const 
 
 // Persistent: every workgroup (one wave) takes triangles from the queues until
 // all are done; triangles it cannot finish go to C.redo.
-template <bool DENS, bool POW>
+template <bool DENS, bool POW, bool GRAD>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) tri_kernel(GridView G, DomainView D, const CellsDev *__restrict__ Cp) {
   __shared__ TriSweepLds S;
   const CellsDev &C = *Cp;
@@ -459,7 +459,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
     // the triangle's own diagram (a batch) or the only one
     const int b = D.nb > 1 ? diagram_of(D.simp_off, D.nb, a) : 0;
     bool written;
-    const bool ok = do_tri<DENS, POW>(S, G.views[b], D.views[b], C, a, written);
+    const bool ok = do_tri<DENS, POW, GRAD>(S, G.views[b], D.views[b], C, a, written);
     if (vd_lane() == 0) {
       GL(C.voided)[a] = !ok && written ? 1 : 0;
       if (!ok)
@@ -492,7 +492,7 @@ int resident_workgroups() {
   int &w = cache[dev];
   if (!w) {
     int per_cu = 0, ncu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tri_kernel<false, false>, 64, 0) != hipSuccess || per_cu < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tri_kernel<false, false, false>, 64, 0) != hipSuccess || per_cu < 1)
       per_cu = 1;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) ncu = 1;
     w = per_cu * ncu;
@@ -508,11 +508,13 @@ int vd_tri_workgroups(long long m) {
 }
 
 void vd_launch_tri(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
-                   bool power, hipStream_t st) {
+                   bool power, bool grad, hipStream_t st) {
   const dim3 grid((unsigned)workgroups), block(64);
-  if (power) hipLaunchKernelGGL((tri_kernel<false, true>), grid, block, 0, st, G, D, Cdev);
-  else if (density) hipLaunchKernelGGL((tri_kernel<true, false>), grid, block, 0, st, G, D, Cdev);
-  else hipLaunchKernelGGL((tri_kernel<false, false>), grid, block, 0, st, G, D, Cdev);
+  if (power) hipLaunchKernelGGL((tri_kernel<false, true, false>), grid, block, 0, st, G, D, Cdev);
+  else if (density && grad) hipLaunchKernelGGL((tri_kernel<true, false, true>), grid, block, 0, st, G, D, Cdev);
+  else if (density) hipLaunchKernelGGL((tri_kernel<true, false, false>), grid, block, 0, st, G, D, Cdev);
+  else if (grad) hipLaunchKernelGGL((tri_kernel<false, false, true>), grid, block, 0, st, G, D, Cdev);
+  else hipLaunchKernelGGL((tri_kernel<false, false, false>), grid, block, 0, st, G, D, Cdev);
 }
 
 void vd_launch_void_triangles(const CellsDev *Cdev, hipStream_t st) {

@@ -522,7 +522,7 @@ __device__ __forceinline__ void face_moments(SweepLds &S, const Poly &Q, const C
 // Returns false when the site has to go to the general kernel (pcount is
 // negative if some of its pieces have been written).
 // ---------------------------------------------------------------------------
-template <bool DENS, bool POW, bool CORNERS, bool LOOSE>
+template <bool DENS, bool POW, bool CORNERS, bool LOOSE, bool GRAD>
 __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const DomainView &D, const CellsDev &C, int si) {
   const int l = vd_lane();
   SiteCtx X;
@@ -570,6 +570,12 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     }
   }
   uint64_t nbmask = 0, cellpos = 0;
+  // face moments (want_grad): the faces of a cell inside M are taken whole, once,
+  // so a piece's wait until a piece has met the boundary (touched); lane k keeps
+  // the slot and the tetrahedron of the k-th piece that waits
+  int nwait = 0, wait_a = 0, nlate = 0;
+  long long wait_p = 0;
+  bool touched = false;
   unsigned sum_faces = 0, sum_verts = 0, dropped = 0;
   Poly cell;
   bool whole = false, loose = false;  // loose: some corners of the cell are not certified
@@ -641,7 +647,7 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     head = nt;
   }
 #pragma unroll 1
-  while (uni((whole || head < nt) && !err)) {
+  while (uni((whole || head < nt || (GRAD && nlate < nwait)) && !err)) {
     int a = -1;
     cell.M = uni64(cell.M);
     free_planes = uni64(free_planes);
@@ -655,11 +661,24 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     dropped = uni(dropped);
     whole = uni(whole);
     if (LOOSE) loose = uni(loose);
+    if (GRAD) {
+      nwait = uni(nwait);
+      nlate = uni(nlate);
+      touched = uni(touched);
+    }
+    const bool late = GRAD && uni(!whole && head >= nt);  // the face moments of what waits
+    long long pidx = -1, fb = 0;
     Poly Q = cell;
-    if (!whole) {
+    if (late) {
+      pidx = readlane_ll(wait_p, nlate);
+      a = touched ? __builtin_amdgcn_readlane(wait_a, nlate) : -1;
+      nlate = touched ? nlate + 1 : nwait;
+    } else if (!whole) {
       a = head < kT ? S.tq[head] : GL(C.tq_spill)[spill + head - kT];
       a = uni(a);
       head++;
+    }
+    if (a >= 0) {
       if (l < 4) {
         double pl[4];
         int lab;
@@ -678,7 +697,7 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
         if (!O) continue;
         if (O == Q.M) { empty = true; break; }
         if (!cut(S, Q, O, f, n, c, bad)) { bad = 1; break; }
-        st.clips++;
+        st.clips += late ? 0 : 1;
       }
       if (bad) { err = 9; break; }
       if (empty) continue;
@@ -701,61 +720,88 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     // chain of LDS round trips is what it costs either way (25.7 ms of 26.3 on
     // the 1M clustered workload) ----
     const uint64_t fmask = faces_of(S, Q);
+    uint64_t bis = GRAD ? fmask & cellpos : 0ull;  // its bisector faces
     const bool live = in_mask(Q.M);
-    const int first = __ffsll((unsigned long long)Q.M) - 1;
-    const double o0 = readlane_d(Q.y0, first), o1 = readlane_d(Q.y1, first), o2 = readlane_d(Q.y2, first);
-    if (live) { S.F.y[l][0] = Q.y0 - o0; S.F.y[l][1] = Q.y1 - o1; S.F.y[l][2] = Q.y2 - o2; }
-    const int T = list_triangles(S, Q, first);
     double pv = 0, pmx = 0, pmy = 0, pmz = 0, pe = 0;
-    double dm = 0;  // (DENS: the moments are weighted, pv is the volume)
-    ConeDensity cd;
-    if (DENS) cd = cone_density(C.dens, X.vx + o0, X.vy + o1, X.vz + o2);
+    const int nc = __popcll(Q.M), nface = __popcll(fmask);
+    long long fo = 0, vo = 0;
+    bool now = late;  // its face moments
+    if (late) {
+      fb = arena_take(S.ar, C, AR_FINT, __popcll(bis));
+    } else {
+      const int first = __ffsll((unsigned long long)Q.M) - 1;
+      const double o0 = readlane_d(Q.y0, first), o1 = readlane_d(Q.y1, first), o2 = readlane_d(Q.y2, first);
+      if (live) { S.F.y[l][0] = Q.y0 - o0; S.F.y[l][1] = Q.y1 - o1; S.F.y[l][2] = Q.y2 - o2; }
+      const int T = list_triangles(S, Q, first);
+      double dm = 0;  // (DENS: the moments are weighted, pv is the volume)
+      ConeDensity cd;
+      if (DENS) cd = cone_density(C.dens, X.vx + o0, X.vy + o1, X.vz + o2);
 #pragma unroll 1
-    for (int t0 = 0; t0 < T; t0 += 64) {
-      if (t0 + l < T) {
-        const unsigned tri = S.F.tri[t0 + l];
-        const double *P = S.F.y[tri & 255], *Y = S.F.y[(tri >> 8) & 255], *Z = S.F.y[tri >> 16];
-        const double p[3] = {P[0], P[1], P[2]}, y[3] = {Y[0], Y[1], Y[2]}, z[3] = {Z[0], Z[1], Z[2]};
-        // 6 vol of (0, p, y, z)
-        const double det = p[0] * (y[1] * z[2] - y[2] * z[1]) - p[1] * (y[0] * z[2] - y[2] * z[0]) +
-                           p[2] * (y[0] * z[1] - y[1] * z[0]);
-        pv += det;
-        if (DENS) {
-          cone_density_moments(cd, p, y, z, det, dm, pmx, pmy, pmz, pe);
-        } else {
-          const double s0 = p[0] + y[0] + z[0], s1 = p[1] + y[1] + z[1], s2 = p[2] + y[2] + z[2];
-          pmx += det * s0; pmy += det * s1; pmz += det * s2;
-          pe += det * (p[0] * p[0] + p[1] * p[1] + p[2] * p[2] + y[0] * y[0] + y[1] * y[1] + y[2] * y[2] +
-                       z[0] * z[0] + z[1] * z[1] + z[2] * z[2] + s0 * s0 + s1 * s1 + s2 * s2);
+      for (int t0 = 0; t0 < T; t0 += 64) {
+        if (t0 + l < T) {
+          const unsigned tri = S.F.tri[t0 + l];
+          const double *P = S.F.y[tri & 255], *Y = S.F.y[(tri >> 8) & 255], *Z = S.F.y[tri >> 16];
+          const double p[3] = {P[0], P[1], P[2]}, y[3] = {Y[0], Y[1], Y[2]}, z[3] = {Z[0], Z[1], Z[2]};
+          // 6 vol of (0, p, y, z)
+          const double det = p[0] * (y[1] * z[2] - y[2] * z[1]) - p[1] * (y[0] * z[2] - y[2] * z[0]) +
+                             p[2] * (y[0] * z[1] - y[1] * z[0]);
+          pv += det;
+          if (DENS) {
+            cone_density_moments(cd, p, y, z, det, dm, pmx, pmy, pmz, pe);
+          } else {
+            const double s0 = p[0] + y[0] + z[0], s1 = p[1] + y[1] + z[1], s2 = p[2] + y[2] + z[2];
+            pmx += det * s0; pmy += det * s1; pmz += det * s2;
+            pe += det * (p[0] * p[0] + p[1] * p[1] + p[2] * p[2] + y[0] * y[0] + y[1] * y[1] + y[2] * y[2] +
+                         z[0] * z[0] + z[1] * z[1] + z[2] * z[2] + s0 * s0 + s1 * s1 + s2 * s2);
+          }
+        }
+      }
+      if (DENS) {
+        pv = readlane_d(blocks_sum(block_sum(pv)), 0);
+      } else {
+        dm = pv;
+      }
+      wave_sum4(dm, pmx, pmy, pmz);
+      pe = readlane_d(blocks_sum(block_sum(pe)), 0);
+      if (!DENS) pv = dm;
+      // a piece exists when its volume is positive; with a density its moments
+      // are the weighted ones
+      if (!(pv > 0.0)) {
+        if (whole) break;
+        continue;
+      }
+      // from o to v_i
+      pv = dm * (1.0 / 6.0);
+      pmx *= DENS ? 1.0 / 6.0 : 1.0 / 24.0; pmy *= DENS ? 1.0 / 6.0 : 1.0 / 24.0; pmz *= DENS ? 1.0 / 6.0 : 1.0 / 24.0;
+      pe = pe * (DENS ? 1.0 / 6.0 : 1.0 / 120.0) + 2.0 * (o0 * pmx + o1 * pmy + o2 * pmz) + (o0 * o0 + o1 * o1 + o2 * o2) * pv;
+      pmx += o0 * pv; pmy += o1 * pv; pmz += o2 * pv;
+      if (l == 0) { S.acc[0] += pv; S.acc[1] += pmx; S.acc[2] += pmy; S.acc[3] += pmz; S.acc[4] += pe; }
+      // ---- emit the piece ----
+      if (GRAD) {
+        touched = touched | (LOOSE && loose) | (nwait == 64) |
+                  (lanes((l >= kPC) & (l < kP) & (S.plab[l < kP ? l : 0] <= VD_BND_BASE + 3)) & fmask) != 0;
+        now = whole || touched;
+      }
+      if (!now) bis = 0;
+      const long long at = arena_take_all(S.ar, C, arena_counts(1, C.emit ? nface : 0, C.emit ? nc : 0, __popcll(bis)));
+      pidx = readlane_ll(at, AR_PIECE);
+      fb = readlane_ll(at, AR_FINT);
+      fo = readlane_ll(at, AR_FACE);
+      vo = readlane_ll(at, AR_VERT);
+      if (GRAD && !now) {
+        if (l == nwait) {
+          wait_a = a;
+          wait_p = pidx;
+        }
+        nwait++;
+        if (l == 0 && pidx < C.cap_piece) {
+          GL(C.piece_fint_start)[pidx] = 0;
+          GL(C.piece_nfint)[pidx] = 0;
         }
       }
     }
-    if (DENS) {
-      pv = readlane_d(blocks_sum(block_sum(pv)), 0);
-    } else {
-      dm = pv;
-    }
-    wave_sum4(dm, pmx, pmy, pmz);
-    pe = readlane_d(blocks_sum(block_sum(pe)), 0);
-    if (!DENS) pv = dm;
-    // a piece exists when its volume is positive; with a density its moments
-    // are the weighted ones
-    if (!(pv > 0.0)) {
-      if (whole) break;
-      continue;
-    }
-    // from o to v_i
-    pv = dm * (1.0 / 6.0);
-    pmx *= DENS ? 1.0 / 6.0 : 1.0 / 24.0; pmy *= DENS ? 1.0 / 6.0 : 1.0 / 24.0; pmz *= DENS ? 1.0 / 6.0 : 1.0 / 24.0;
-    pe = pe * (DENS ? 1.0 / 6.0 : 1.0 / 120.0) + 2.0 * (o0 * pmx + o1 * pmy + o2 * pmz) + (o0 * o0 + o1 * o1 + o2 * o2) * pv;
-    pmx += o0 * pv; pmy += o1 * pv; pmz += o2 * pv;
-    if (l == 0) { S.acc[0] += pv; S.acc[1] += pmx; S.acc[2] += pmy; S.acc[3] += pmz; S.acc[4] += pe; }
-    // ---- emit the piece ----
-    const int nc = __popcll(Q.M), nface = __popcll(fmask);
-    const uint64_t bis = C.want_grad ? fmask & cellpos : 0ull;  // its bisector faces
-    const long long at = arena_take_all(S.ar, C, arena_counts(1, C.emit ? nface : 0, C.emit ? nc : 0, __popcll(bis)));
-    const long long pidx = readlane_ll(at, AR_PIECE), fo = readlane_ll(at, AR_FACE), vo = readlane_ll(at, AR_VERT);
-    if (C.want_grad) face_moments<DENS>(S, Q, C, X, pidx, bis, readlane_ll(at, AR_FINT));
+    if (GRAD && now) face_moments<DENS>(S, Q, C, X, pidx, bis, fb);
+    if (late) continue;
     // a record that does not fit its arena is dropped and counted; the per-site
     // counts below only count what was written, so the CSR built from them
     // stays inside the arenas (the clip then reports VD_ERR_CAPACITY)
@@ -858,8 +904,10 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
 // DENS: moments weighted by the density; POW: power diagrams; CORNERS: the
 // interior split by the cells' corners; LOOSE: a clip with boundary seeds (M is
 // not convex or a site lies outside it),
-// where cells that reach far out of it are certified piece by piece.
-template <bool DENS, bool POW, bool CORNERS, bool LOOSE>
+// where cells that reach far out of it are certified piece by piece; GRAD: face
+// moments (the instances without them are shorter and spill less: 25.7 against
+// 27.6 ms on the 1M clustered workload).
+template <bool DENS, bool POW, bool CORNERS, bool LOOSE, bool GRAD>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) sweep_kernel(GridView G, DomainView D, const CellsDev *__restrict__ Cp) {
   __shared__ SweepLds S;
   const CellsDev &C = *Cp;
@@ -868,7 +916,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
     const int si = queue_next(S.ar, C, G.n);
     if (si < 0) break;
     const int b = G.nb > 1 ? diagram_of(G.site_off, G.nb, si) : 0;
-    if (!do_cell<DENS, POW, CORNERS, LOOSE>(S, G.views[b], D.views[b], C, si) && vd_lane() == 0)
+    if (!do_cell<DENS, POW, CORNERS, LOOSE, GRAD>(S, G.views[b], D.views[b], C, si) && vd_lane() == 0)
       GL(C.redo)[__hip_atomic_fetch_add(GL(C.cnt) + CNT_REDO, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = si;
   }
   arena_close(S.ar, C);
@@ -893,7 +941,7 @@ int resident_workgroups() {
   int &w = cache[dev];
   if (!w) {
     int per_cu = 0, ncu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sweep_kernel<false, false, false, false>, 64, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sweep_kernel<false, false, false, false, false>, 64, 0) != hipSuccess ||
         per_cu < 1)
       per_cu = 1;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) ncu = 1;
@@ -910,15 +958,24 @@ int vd_sweep_workgroups(long long n) {
 }
 
 void vd_launch_sweep(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
-                     bool power, bool corners, bool bseeds, hipStream_t st) {
+                     bool power, bool corners, bool bseeds, bool grad, hipStream_t st) {
   const dim3 grid(workgroups), block(64);
-  if (power) hipLaunchKernelGGL((sweep_kernel<false, true, false, false>), grid, block, 0, st, G, D, Cdev);
-  else if (density && corners) hipLaunchKernelGGL((sweep_kernel<true, false, true, false>), grid, block, 0, st, G, D, Cdev);
-  else if (corners) hipLaunchKernelGGL((sweep_kernel<false, false, true, false>), grid, block, 0, st, G, D, Cdev);
-  else if (density && !bseeds) hipLaunchKernelGGL((sweep_kernel<true, false, false, false>), grid, block, 0, st, G, D, Cdev);
-  else if (density) hipLaunchKernelGGL((sweep_kernel<true, false, false, true>), grid, block, 0, st, G, D, Cdev);
-  else if (!bseeds) hipLaunchKernelGGL((sweep_kernel<false, false, false, false>), grid, block, 0, st, G, D, Cdev);
-  else hipLaunchKernelGGL((sweep_kernel<false, false, false, true>), grid, block, 0, st, G, D, Cdev);
+#define VD_SWEEP(dens, pow, cor, loose, gr) \
+  hipLaunchKernelGGL((sweep_kernel<dens, pow, cor, loose, gr>), grid, block, 0, st, G, D, Cdev)
+#define VD_SWEEP_GRAD(dens, cor, loose)             \
+  do {                                              \
+    if (grad) VD_SWEEP(dens, false, cor, loose, true); \
+    else VD_SWEEP(dens, false, cor, loose, false);  \
+  } while (0)
+  if (power) VD_SWEEP(false, true, false, false, false);
+  else if (density && corners) VD_SWEEP_GRAD(true, true, false);
+  else if (corners) VD_SWEEP_GRAD(false, true, false);
+  else if (density && !bseeds) VD_SWEEP_GRAD(true, false, false);
+  else if (density) VD_SWEEP_GRAD(true, false, true);
+  else if (!bseeds) VD_SWEEP_GRAD(false, false, false);
+  else VD_SWEEP_GRAD(false, false, true);
+#undef VD_SWEEP_GRAD
+#undef VD_SWEEP
 }
 
 void vd_launch_void_pieces(const CellsDev *Cdev, hipStream_t st) {

@@ -464,13 +464,13 @@ void vd_launch_sites3d(const GridView &G, const DomainView &D, const CellsDev *C
 // leaves in Cdev->redo are then taken by vd_launch_sites3d with redo = true
 int vd_sweep_workgroups(long long n);
 void vd_launch_sweep(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
-                     bool power, bool corners, bool bseeds, hipStream_t st);
+                     bool power, bool corners, bool bseeds, bool grad, hipStream_t st);
 void vd_launch_void_pieces(const CellsDev *Cdev, hipStream_t st);  // between the two: drops half-done sites' pieces
 // the same for surfaces: sweep kernel, drop of half-done triangles' pieces, and
 // the searched kernel (of all triangles, or of those the sweep left)
 int vd_tri_workgroups(long long m);
 void vd_launch_tri(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
-                   bool power, hipStream_t st);
+                   bool power, bool grad, hipStream_t st);
 void vd_launch_void_triangles(const CellsDev *Cdev, hipStream_t st);
 int vd_surface_workgroups(long long m);
 void vd_launch_surface(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool density,
