@@ -75,13 +75,6 @@ hipError_t ensure_fixed(T *&p, int64_t n) {
   return BlockPool::get().alloc((void **)&p, sizeof(T) * (size_t)std::max<int64_t>(n, 1));
 }
 
-__global__ void reset_counters(unsigned long long *cnt) {
-  const int i = threadIdx.x;
-  if (i < CNT_N)
-    cnt[i] = (i == CNT_BAD_SITE) ? 0x7fffffffull
-                                 : (i == CNT_MINMARGIN ? (unsigned long long)__double_as_longlong(1.0) : 0ull);
-}
-
 hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
 }  // namespace
@@ -949,7 +942,6 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     const int64_t caps[AR_N] = {d.cap_piece, d.cap_face, d.cap_vert, d.cap_nbr, d.cap_fint};
     for (int r = 0; r < AR_N; r++)
       d.chunk[r] = std::max<int64_t>(1, std::min<int64_t>(4096, caps[r] / (c->div * (int64_t)wg)));
-    hipLaunchKernelGGL(reset_counters, dim3(1), dim3(64), 0, st, d.cnt);
     // batches: the diagrams with the most tetrahedra per site first (below)
     d.order = nullptr;
     if (dom->dim == 3 && g->nb > 1 && opt.batch_order) {
@@ -964,7 +956,11 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
         for (int k = 0; k <= VD_QUEUES; k++) d.qoff[k] = c->order_qoff[k];
       }
     }
-    vd_launch_queue_init(d.queue, items, d.order ? d.qoff : nullptr, st);
+    // seeds are made by the first attempt
+    const bool seeds = dom->dim == 3 && attempt == 0;
+    if (seeds) HIP_TRY(ensure_fixed(c->outside, 6));
+    vd_launch_clip_begin(d.cnt, d.queue, items, d.order ? d.qoff : nullptr, seeds ? c->outside : nullptr,
+                         dom->dim == 2 ? d.pcount : nullptr, n, st);
     GridView G = g->view();
     DomainView D = dom->view();
     if (opt.time_kernels && !c->ev0) {
@@ -977,15 +973,10 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
       c->d_shadow = d;
       HIP_TRY(hipMemcpyAsync(c->d_dev, &c->d_shadow, sizeof(CellsDev), hipMemcpyHostToDevice, st));
     }
-    if (dom->dim == 3 && attempt == 0) {
+    if (seeds) {
       // seeds: the tetrahedron holding each site, and (Alg. 5) the boundary
       // triangles each cell meets when the domain is not convex or a site
       // lies outside it
-      HIP_TRY(ensure_fixed(c->outside, 6));
-      for (int k = 0; k < 6; k += 2) {
-        vd_launch_fill_int(c->outside + k, 1, 0, st);
-        vd_launch_fill_int(c->outside + k + 1, 1, INT_MAX, st);
-      }
       vd_launch_locate_sites(G, D, d.seed, c->outside, st);
       bool use_b = false;
       c->sites_outside = -1;
@@ -1045,7 +1036,6 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
         HIP_TRY(hipMemcpyAsync(c->d_dev, &c->d_shadow, sizeof(CellsDev), hipMemcpyHostToDevice, st));
       }
     }
-    if (dom->dim == 2) vd_launch_fill_int(d.pcount, n, 0, st);
     if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev0, st));
     if (dom->dim == 2 && sweep) vd_launch_tri(G, D, c->d_dev, wg, opt.use_density != 0, g->power, opt.want_grad != 0, st);
     else if (dom->dim == 2) vd_launch_surface(G, D, c->d_dev, wg, opt.use_density != 0, g->power, false, st);

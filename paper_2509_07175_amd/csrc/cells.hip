@@ -189,8 +189,15 @@ void vd_launch_finalize(vd_cells c, hipStream_t st) {
   const unsigned long long *cnt = (const unsigned long long *)d.cnt;
   const long long groups = (n + 4 * kSortWaves - 1) / (4 * kSortWaves);
   const unsigned nsort = (unsigned)std::max<long long>(1, std::min<long long>(groups, 8192));
-  vdscan::exclusive_scan<int, long long>(d.pcount, n, c->piece_off, c->scan_tmp, st);
-  vd_launch_fill_int(c->fillc, n, 0, st);
+  const bool one = n <= vdscan::kOne;  // one launch for what else takes four, or in 3D seven
+  if (one) {
+    const vdscan::ScanJob<int, long long> pieces{d.pcount, c->piece_off, c->fillc}, nbrs{d.ncount, c->nbr_off, nullptr};
+    hipLaunchKernelGGL((vdscan::one_scan<int, long long>), dim3(c->dim == 3 ? 2 : 1), dim3(vdscan::kOneThreads), 0, st, n,
+                       pieces, nbrs);
+  } else {
+    vdscan::exclusive_scan<int, long long>(d.pcount, n, c->piece_off, c->scan_tmp, st);
+    vd_launch_fill_int(c->fillc, n, 0, st);
+  }
   if (c->dim == 3) {
     // each site's pieces from its run of slots, ranked by simplex; the few
     // sites whose pieces span runs are grouped first
@@ -203,7 +210,7 @@ void vd_launch_finalize(vd_cells c, hipStream_t st) {
     hipLaunchKernelGGL(sort_segments, dim3(nsort), dim3(kB), 0, st, n, (const long long *)c->piece_off,
                        (const int *)d.piece_simplex, (const int *)c->fillc, (const unsigned long long *)run,
                        (const int *)c->pid_tmp, c->piece_id);
-    vdscan::exclusive_scan<int, long long>(d.ncount, n, c->nbr_off, c->scan_tmp, st);
+    if (!one) vdscan::exclusive_scan<int, long long>(d.ncount, n, c->nbr_off, c->scan_tmp, st);
     hipLaunchKernelGGL(gather_lists, dim3(blocks(n * kGroup)), dim3(kB), 0, st, n, (const int *)d.ncount,
                        (const long long *)d.nstart, (const int *)d.nbr_arena, (const long long *)c->nbr_off,
                        c->nbr);

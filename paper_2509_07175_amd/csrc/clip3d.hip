@@ -41,6 +41,8 @@
 // wave with butterfly shuffles (fixed order, no floating-point atomics).
 #include <type_traits>
 
+#include <climits>
+
 #include "vd_site.h"
 
 namespace {
@@ -1454,11 +1456,22 @@ struct QueueStarts {
   long long off[VD_QUEUES];
   int given;
 };
-__global__ void queue_init(int *q, long long n, QueueStarts qs) {
+// Before a clip: counters, queue heads, the counts of sites outside M, not
+// finite and repeated (`outside`, with the first of each; nullable), and n ints
+// of `zero` (nullable), in one launch: small clips are bound by their launches.
+__global__ void __launch_bounds__(256) clip_begin(unsigned long long *cnt, int *q, long long items, QueueStarts qs,
+                                                  int *outside, int *zero, long long n) {
   const int k = threadIdx.x;
-  const long long q8 = (n + VD_QUEUES - 1) / VD_QUEUES;
-  if (k < VD_QUEUES) q[k * VD_QSTRIDE] = (int)(qs.given ? qs.off[k] : (k * q8 < n ? k * q8 : n));
+  if (zero)
+    for (long long i = (long long)blockIdx.x * 256 + k; i < n; i += (long long)gridDim.x * 256) zero[i] = 0;
+  if (blockIdx.x) return;
+  if (k < CNT_N)
+    cnt[k] = (k == CNT_BAD_SITE) ? 0x7fffffffull
+                                 : (k == CNT_MINMARGIN ? (unsigned long long)__double_as_longlong(1.0) : 0ull);
+  const long long q8 = (items + VD_QUEUES - 1) / VD_QUEUES;
+  if (k < VD_QUEUES) q[k * VD_QSTRIDE] = (int)(qs.given ? qs.off[k] : (k * q8 < items ? k * q8 : items));
   if (k == VD_QREDO) q[k * VD_QSTRIDE] = 0;
+  if (outside && k < 6) outside[k] = k & 1 ? INT_MAX : 0;
 }
 
 int resident_workgroups() {
@@ -1485,12 +1498,15 @@ int vd_sites3d_workgroups(long long n) {
 }
 
 // qoff: the first position of each queue in the batch's work order, or NULL
-void vd_launch_queue_init(int *queue, long long n, const long long *qoff, hipStream_t st) {
+void vd_launch_clip_begin(unsigned long long *cnt, int *queue, long long items, const long long *qoff, int *outside,
+                          int *zero, long long n, hipStream_t st) {
   QueueStarts qs{};
   qs.given = qoff ? 1 : 0;
   if (qoff)
     for (int k = 0; k < VD_QUEUES; k++) qs.off[k] = qoff[k];
-  hipLaunchKernelGGL(queue_init, dim3(1), dim3(64), 0, st, queue, n, qs);
+  const long long nb = zero ? (n + 1023) / 1024 : 1;
+  hipLaunchKernelGGL(clip_begin, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(256), 0, st, cnt, queue, items, qs,
+                     outside, zero, n);
 }
 
 void vd_launch_sites3d(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool monitor,

@@ -15,8 +15,16 @@ namespace {
 
 constexpr int kB = 256;
 
+// clears the per-cell counters of the sort (this thread's share)
+__device__ __forceinline__ void clear_cells(long long ncell, int *__restrict__ count, int *__restrict__ fill) {
+  for (long long c = (long long)blockIdx.x * kB + threadIdx.x; c < ncell; c += (long long)gridDim.x * kB)
+    count[c] = fill[c] = 0;
+}
+
 __global__ void __launch_bounds__(kB) bbox_partial(const double *__restrict__ s, long long n,
-                                                   double *__restrict__ part) {
+                                                   double *__restrict__ part, long long ncell,
+                                                   int *__restrict__ count, int *__restrict__ fill) {
+  clear_cells(ncell, count, fill);
   double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
   for (long long i = (long long)blockIdx.x * kB + threadIdx.x; i < n; i += (long long)gridDim.x * kB) {
     for (int k = 0; k < 3; k++) {
@@ -65,23 +73,28 @@ __global__ void __launch_bounds__(kB) bbox_seg(const double *__restrict__ s, con
   if (threadIdx.x < 6) part[6 * b + threadIdx.x] = red[threadIdx.x][0];
 }
 
-// Geometry of diagram b (thread b): the union of its sites' box (ppd partial
-// boxes) and the caller's box (user, nullable), padded so points on the upper
-// faces fall inside the last cells; h = extent / cells.
-__global__ void grid_geom(const double *__restrict__ part, int ppd, int nb, const double *__restrict__ user,
-                          const int *__restrict__ dims, double *__restrict__ geom) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb) return;
+// Geometry of diagram b (block b, one wave): the union of its sites' box (ppd
+// partial boxes, read by the lanes: one thread took 47 us for the 256 of a
+// single diagram) and the caller's box (user, nullable), padded so points on
+// the upper faces fall inside the last cells; h = extent / cells.
+__global__ void __launch_bounds__(64) grid_geom(const double *__restrict__ part, int ppd, const double *__restrict__ user,
+                                                const int *__restrict__ dims, double *__restrict__ geom) {
+  const int b = blockIdx.x;
   double lo[3], hi[3];
   for (int k = 0; k < 3; k++) {
     lo[k] = user ? user[6 * b + k] : 1e300;
     hi[k] = user ? user[6 * b + 3 + k] : -1e300;
   }
-  for (int q = 0; q < ppd; q++)
+  for (int q = threadIdx.x; q < ppd; q += 64)
     for (int k = 0; k < 3; k++) {
       lo[k] = fmin(lo[k], part[6 * (b * ppd + q) + k]);
       hi[k] = fmax(hi[k], part[6 * (b * ppd + q) + 3 + k]);
     }
+  for (int k = 0; k < 3; k++) {
+    lo[k] = wave_min(lo[k]);
+    hi[k] = -wave_min(-hi[k]);
+  }
+  if (threadIdx.x > 0) return;
   double ext = 0;
   for (int k = 0; k < 3; k++) ext = fmax(ext, hi[k] - lo[k]);
   if (!(ext > 0)) ext = 1.0;
@@ -99,7 +112,9 @@ __global__ void grid_geom(const double *__restrict__ part, int ppd, int nb, cons
 
 // diagram of every caller index
 __global__ void __launch_bounds__(kB) site_diag(long long n, const long long *__restrict__ off, int nb,
-                                                int *__restrict__ diag) {
+                                                int *__restrict__ diag, long long ncell, int *__restrict__ count,
+                                                int *__restrict__ fill) {
+  clear_cells(ncell, count, fill);
   const long long i = (long long)blockIdx.x * kB + threadIdx.x;
   if (i < n) diag[i] = diagram_of(off, nb, i);
 }
@@ -137,10 +152,11 @@ __global__ void __launch_bounds__(kB) grid_scatter(const double *__restrict__ s,
 }
 
 // Order the sites of each cell by the caller's index (insertion sort; cells
-// hold a handful of sites at the target density).
+// hold a handful of sites at the target density), and their ranks.
 __global__ void __launch_bounds__(kB) grid_sort_cells(long long ncell, const int *__restrict__ cstart,
                                                       double *__restrict__ sx, double *__restrict__ sy,
-                                                      double *__restrict__ sz, int *__restrict__ perm) {
+                                                      double *__restrict__ sz, int *__restrict__ perm,
+                                                      int *__restrict__ rank) {
   const long long c = (long long)blockIdx.x * kB + threadIdx.x;
   if (c >= ncell) return;
   const int a = cstart[c], b = cstart[c + 1];
@@ -154,12 +170,7 @@ __global__ void __launch_bounds__(kB) grid_sort_cells(long long ncell, const int
     }
     perm[j + 1] = key; sx[j + 1] = x; sy[j + 1] = y; sz[j + 1] = z;
   }
-}
-
-__global__ void __launch_bounds__(kB) grid_rank(long long n, const int *__restrict__ perm,
-                                                int *__restrict__ rank) {
-  const long long p = (long long)blockIdx.x * kB + threadIdx.x;
-  if (p < n) rank[perm[p]] = (int)p;
+  for (int i = a; i < b; i++) rank[perm[i]] = i;
 }
 
 __global__ void __launch_bounds__(kB) grid_delta(GridView G, double *__restrict__ delta) {
@@ -216,24 +227,22 @@ void vd_launch_grid_weights(vd_grid g, const double *w, int *flags, hipStream_t 
                      (const double *)g->eta, g->sh);
 }
 
-void vd_launch_fill_int(int *p, long long n, int v, hipStream_t st);
-
 void vd_launch_grid_build(vd_grid g, const double *sites, const double *user_box, hipStream_t st) {
   const long long n = g->n;
   const int nb = g->nb;
   int ppd;
   if (nb == 1) {
     ppd = 256;
-    hipLaunchKernelGGL(bbox_partial, dim3(ppd), dim3(kB), 0, st, sites, n, g->bbox_part);
+    hipLaunchKernelGGL(bbox_partial, dim3(ppd), dim3(kB), 0, st, sites, n, g->bbox_part,
+                       (long long)g->ncell, g->ccount, g->fill);
   } else {
     ppd = 1;
     hipLaunchKernelGGL(bbox_seg, dim3(nb), dim3(kB), 0, st, sites, (const long long *)g->d_site_off, g->bbox_part);
-    hipLaunchKernelGGL(site_diag, dim3(blocks(n)), dim3(kB), 0, st, n, (const long long *)g->d_site_off, nb, g->diag);
+    hipLaunchKernelGGL(site_diag, dim3(blocks(n)), dim3(kB), 0, st, n, (const long long *)g->d_site_off, nb, g->diag,
+                       (long long)g->ncell, g->ccount, g->fill);
   }
-  hipLaunchKernelGGL(grid_geom, dim3((nb + 63) / 64), dim3(64), 0, st, (const double *)g->bbox_part, ppd, nb,
+  hipLaunchKernelGGL(grid_geom, dim3(nb), dim3(64), 0, st, (const double *)g->bbox_part, ppd,
                      user_box, (const int *)g->d_dims, g->geom);
-  vd_launch_fill_int(g->ccount, g->ncell, 0, st);
-  vd_launch_fill_int(g->fill, g->ncell, 0, st);
   hipLaunchKernelGGL(grid_hist, dim3(blocks(n)), dim3(kB), 0, st, sites, n, nb == 1 ? (const int *)nullptr : g->diag,
                      (const double *)g->geom, (const int *)g->d_dims, (const long long *)g->d_cell_off, g->cellid,
                      g->ccount);
@@ -241,8 +250,7 @@ void vd_launch_grid_build(vd_grid g, const double *sites, const double *user_box
   hipLaunchKernelGGL(grid_scatter, dim3(blocks(n)), dim3(kB), 0, st, sites, n, (const int *)g->cellid,
                      (const int *)g->cstart, g->fill, g->sx, g->sy, g->sz, g->perm);
   hipLaunchKernelGGL(grid_sort_cells, dim3(blocks(g->ncell)), dim3(kB), 0, st, (long long)g->ncell,
-                     (const int *)g->cstart, g->sx, g->sy, g->sz, g->perm);
-  hipLaunchKernelGGL(grid_rank, dim3(blocks(n)), dim3(kB), 0, st, n, (const int *)g->perm, g->rank);
+                     (const int *)g->cstart, g->sx, g->sy, g->sz, g->perm, g->rank);
   g->delta_valid = false;
 }
 

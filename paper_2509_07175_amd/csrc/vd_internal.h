@@ -49,7 +49,7 @@ enum {
   CNT_N,
   CNT_STATS = CNT_FANTETS - CNT_QUERIES + 1
 };
-static_assert(CNT_N <= 64, "reset_counters clears the counters with one wave");
+static_assert(CNT_N <= 256, "clip_begin clears the counters with one block");
 
 // persistent kernels: one work queue per XCD (8 heads, one per 128-byte line)
 #define VD_QUEUES 8
@@ -457,7 +457,8 @@ void vd_launch_domain_locator(vd_domain d, hipStream_t st);
 void vd_launch_locate_sites(const GridView &G, const DomainView &D, int *seed, int *outside, hipStream_t st);
 // workgroups of the persistent 3D site kernel (resident waves of the device)
 int vd_sites3d_workgroups(long long n);
-void vd_launch_queue_init(int *queue, long long n, const long long *qoff, hipStream_t st);
+void vd_launch_clip_begin(unsigned long long *cnt, int *queue, long long items, const long long *qoff, int *outside,
+                          int *zero, long long n, hipStream_t st);
 void vd_launch_sites3d(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool monitor,
                        bool density, bool power, bool corners, bool redo, hipStream_t st);
 // the default clip: workgroups of the sweep kernel, and its launch; the sites it
