@@ -44,7 +44,7 @@ struct __align__(16) TriSweepLds {
     } R;
     unsigned short pre[kBatch][kNB];
   };
-  union {
+  union alignas(16) {
     struct {
       double s[kK][4];       // sites relative to the centroid, and half their squared norm (power: minus w)
       int p[kK];             // sorted position

@@ -21,14 +21,20 @@
 // the new corners their free lanes, so survivors never move.  Planes and
 // the tables that link the fan of a new face are in LDS.
 //
-// What bounds it: VALU issue (61 to 67 % of the cycles) and, with the rest, the
-// LDS round trips of a cut, which four waves per SIMD overlap (128 VGPRs; five
-// waves at 96 spill more than they hide: 72 against 65 ms on 5M uniform sites).
+// What bounds it: waits for LDS round trips (45 % of a wave's time) and VALU
+// issue (65 % of the cycles), at four waves per SIMD (128 VGPRs; five waves at 96
+// spill: 26.0 against 24.6 ms on the 1M clustered workload, 58.8 against 57.7 on 5M
+// uniform sites).  So reads that do not depend on each other are issued
+// together: the planes of four sites before their tests, the planes of a new
+// corner before the tables that link it, those of up to seven tetrahedra for one
+// chain of mesh reads; and rows of LDS are 16-byte aligned (5M sites 57.7 -> 53.5 ms,
+// 1M clustered 24.6 -> 23.3 ms).  Two pieces at once, one in each half of the wave,
+// or corners placed along the cut edge instead of solved for, gained nothing.
 // All control flow is on scalar values (ballots, readlane): where the compiler
 // cannot see that a value is uniform it is passed through readlane, or every
 // branch behind it would save and restore the exec mask (36 -> 28 ms on the 1M
 // clustered workload).  Against the searched carve: 1M clustered sites in
-// 750,000 tetrahedra 64.7 -> 25 ms, 5M uniform sites 168.6 -> 56 ms.
+// 750,000 tetrahedra 64.7 -> 23 ms, 5M uniform sites 168.6 -> 51 ms.
 //
 // A cell that does not fit (more than 64 corners or 36 planes at a time) or
 // whose cut is degenerate is put on a list that clip3d.hip's kernel works
@@ -40,7 +46,9 @@
 namespace {
 
 constexpr int kPC = 36;      // plane slots of the cell (64 corners have at most 34 faces)
-constexpr int kP = kPC + 4;  // ... and of a tetrahedron
+constexpr int kTB = 7;       // tetrahedra whose planes are computed at a time
+constexpr int kP = kPC + 4 * kTB;  // ... and theirs: a plane to a lane
+static_assert(kP == 64, "masks of planes");
 constexpr int kT = 64;       // simplices of a site held in LDS
 constexpr int kRounds = 3;   // rounds of grid queries for a cell before its pieces are certified instead
 
@@ -61,7 +69,7 @@ struct __align__(16) SweepLds {
   };
   unsigned rec[64];          // new corners: planes u, w and the surviving end of the cut edge
   int tq[kT];                // simplices of the site, breadth-first
-  union {
+  union alignas(16) {  // (whole sites and corners are read 16 bytes at a time)
     struct {
       double s[kK][4];       // sites relative to v_i, and the offset of their bisector
       int p[kK];             // sorted position
@@ -101,10 +109,9 @@ __device__ __forceinline__ uint64_t outside_of(const Poly &Q, const double *n, d
 // the lane of the corner across edge e
 __device__ __forceinline__ int across(const Poly &Q, int e) { return ~(Q.nb >> (8 * e)) & 63; }
 
-// Vertex of the planes in slots u and w and the plane n.y = c, by Cramer's rule.
-__device__ __forceinline__ void vertex_of(const SweepLds &S, int u, int w, const double *n, double c, double &y0,
+// Vertex of the planes n0, n1 (offset last) and n.y = c, by Cramer's rule.
+__device__ __forceinline__ void vertex_of(const double *n0, const double *n1, const double *n, double c, double &y0,
                                           double &y1, double &y2) {
-  const double *n0 = S.pn[u], *n1 = S.pn[w];
   const double c12[3] = {n1[1] * n[2] - n1[2] * n[1], n1[2] * n[0] - n1[0] * n[2], n1[0] * n[1] - n1[1] * n[0]};
   const double c20[3] = {n[1] * n0[2] - n[2] * n0[1], n[2] * n0[0] - n[0] * n0[2], n[0] * n0[1] - n[1] * n0[0]};
   const double c01[3] = {n0[1] * n1[2] - n0[2] * n1[1], n0[2] * n1[0] - n0[0] * n1[2], n0[0] * n1[1] - n0[1] * n1[0]};
@@ -138,15 +145,18 @@ __device__ __forceinline__ bool cut(SweepLds &S, Poly &Q, uint64_t O, int P, con
   lds_order();
   const int rank = mbcnt64(F);
   const uint64_t N = lanes(rank < nnew) & F;
-  unsigned rec = 0;
+  const unsigned rec = S.rec[rank & 63];
+  const int u = in_mask(N) ? rec & 255 : 0, w = in_mask(N) ? (rec >> 8) & 255 : 0;
   if (in_mask(N)) {
-    rec = S.rec[rank];
-    S.first[rec & 255] = (unsigned char)(63 - l);
-    S.second[(rec >> 8) & 255] = (unsigned char)(63 - l);
+    S.first[u] = (unsigned char)(63 - l);
+    S.second[w] = (unsigned char)(63 - l);
   }
+  const double g0[4] = {S.pn[u][0], S.pn[u][1], S.pn[u][2], S.pn[u][3]};
+  const double g1[4] = {S.pn[w][0], S.pn[w][1], S.pn[w][2], S.pn[w][3]};
   lds_order();
   // a surviving end: the edge's new corner has as first plane the edge's second plane seen from here
   const int f0 = S.first[p8(Q.cp, 1)], f1 = S.first[p8(Q.cp, 2)], f2 = S.first[p8(Q.cp, 0)];
+  const int fw = S.first[w], su = S.second[u], fu = S.first[u], sw = S.second[w];
   int nb = Q.nb;
   nb = in_mask(keep & x0) ? (int)__builtin_amdgcn_perm(f0, nb, 0x03020104u) : nb;
   nb = in_mask(keep & x1) ? (int)__builtin_amdgcn_perm(f1, nb, 0x03020400u) : nb;
@@ -154,12 +164,11 @@ __device__ __forceinline__ bool cut(SweepLds &S, Poly &Q, uint64_t O, int P, con
   Q.nb = nb;
   bool wrong = false;
   if (in_mask(N)) {
-    const int u = rec & 255, w = (rec >> 8) & 255;
-    Q.nb = (int)(rec >> 16) | S.first[w] << 8 | S.second[u] << 16;
+    Q.nb = (int)(rec >> 16) | fw << 8 | su << 16;
     Q.cp = (int)(rec & 0xffff) | P << 16;
-    vertex_of(S, u, w, n, c, Q.y0, Q.y1, Q.y2);
+    vertex_of(g0, g1, n, c, Q.y0, Q.y1, Q.y2);
     // two corners with the same first (second) plane: not a simple loop
-    wrong = (S.first[u] != 63 - l) | (S.second[w] != 63 - l) | !isfinite(Q.y0 + Q.y1 + Q.y2);
+    wrong = (fu != 63 - l) | (sw != 63 - l) | !isfinite(Q.y0 + Q.y1 + Q.y2);
   }
   bad |= lanes(wrong);
   Q.M = keep | N;
@@ -177,8 +186,7 @@ __device__ __forceinline__ uint64_t planes_in_use(SweepLds &S, const Poly &Q) {
     S.mark[p8(Q.cp, 2)] = 1;
   }
   lds_order();
-  const bool u = l < kP && S.mark[l < kP ? l : 0];
-  return lanes(u);
+  return lanes(S.mark[l] != 0);
 }
 
 // a free plane slot of the cell, or -1
@@ -256,12 +264,14 @@ __device__ __forceinline__ int sweep(SweepLds &S, const GridView &G, const SiteC
   const int l = vd_lane();
   const double h2 = POW ? X.h * X.h : 0.0;
   uint64_t bad = 0;
-  int k = 0;
+  int k = 0, check = 0;
   for (;;) {
-    // the next site that some corner is nearer to, four at a time
+    // the next site that some corner is nearer to, four at a time: their planes
+    // are read together, for one wait
     uint64_t any = 0;
     while (k < held) {
-      if ((k & 7) == 0) {
+      if (k >= check) {
+        check = k + 8;
         // no site beyond twice the farthest corner is nearer to any corner than v_i
         const float f = wave_fmax(in_mask(Q.M) ? (float)(Q.y0 * Q.y0 + Q.y1 * Q.y1 + Q.y2 * Q.y2) : 0.0f);
         const double R2 = (double)f * (1.0 + 1e-6);
@@ -272,9 +282,17 @@ __device__ __forceinline__ int sweep(SweepLds &S, const GridView &G, const SiteC
         }
         if (uni((double)S.K.kb[k] * S.step > lim * (1.0 + 1e-6))) break;
       }
-      if ((k & 3) == 0 && k + 4 <= held) {
-        const uint64_t o0 = outside_of(Q, S.K.s[k], S.K.s[k][3]), o1 = outside_of(Q, S.K.s[k + 1], S.K.s[k + 1][3]),
-                       o2 = outside_of(Q, S.K.s[k + 2], S.K.s[k + 2][3]), o3 = outside_of(Q, S.K.s[k + 3], S.K.s[k + 3][3]);
+      if (k + 4 <= held) {
+        double g[4][4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          const double2 *e = reinterpret_cast<const double2 *>(S.K.s[k + j]);
+          const double2 e0 = e[0], e1 = e[1];
+          g[j][0] = e0.x; g[j][1] = e0.y; g[j][2] = e1.x; g[j][3] = e1.y;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const uint64_t o0 = outside_of(Q, g[0], g[0][3]), o1 = outside_of(Q, g[1], g[1][3]),
+                       o2 = outside_of(Q, g[2], g[2][3]), o3 = outside_of(Q, g[3], g[3][3]);
         any = o0 | o1 | o2 | o3;
         if (any) {
           k += o0 ? 0 : (o1 ? 1 : (o2 ? 2 : 3));
@@ -375,7 +393,7 @@ __device__ __forceinline__ int ask_grid(SweepLds &S, const GridView &G, const Si
 // planes_in_use for a piece, and the lowest corner of each plane to F.pfirst
 __device__ __forceinline__ uint64_t faces_of(SweepLds &S, const Poly &Q) {
   const int l = vd_lane();
-  if (l < kP) S.F.pfirst[l] = 64;
+  S.F.pfirst[l] = 64;
   lds_order();
   if (in_mask(Q.M)) {
     atomicMin(&S.F.pfirst[p8(Q.cp, 0)], l);
@@ -383,7 +401,7 @@ __device__ __forceinline__ uint64_t faces_of(SweepLds &S, const Poly &Q) {
     atomicMin(&S.F.pfirst[p8(Q.cp, 2)], l);
   }
   lds_order();
-  return lanes(l < kP && S.F.pfirst[l < kP ? l : 0] < 64);
+  return lanes(S.F.pfirst[l] < 64);
 }
 
 // Lists the triangles (lowest corner, corner, next corner) of the faces that do
@@ -574,6 +592,7 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
   // so a piece's wait until a piece has met the boundary (touched); lane k keeps
   // the slot and the tetrahedron of the k-th piece that waits
   int nwait = 0, wait_a = 0, nlate = 0;
+  int pl0 = 0, pl1 = 0;  // the queue entries whose planes are in LDS
   long long wait_p = 0;
   bool touched = false;
   unsigned sum_faces = 0, sum_verts = 0, dropped = 0;
@@ -656,6 +675,8 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     nt = uni(nt);
     head = uni(head);
     npieces = uni(npieces);
+    pl0 = uni(pl0);
+    pl1 = uni(pl1);
     sum_faces = uni(sum_faces);
     sum_verts = uni(sum_verts);
     dropped = uni(dropped);
@@ -678,20 +699,50 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
       a = uni(a);
       head++;
     }
+    int P = kPC;  // the tetrahedron's planes
     if (a >= 0) {
-      if (l < 4) {
-        double pl[4];
-        int lab;
-        tet_plane(D, X, a, l, pl, lab);
-        S.pn[kPC + l][0] = pl[0]; S.pn[kPC + l][1] = pl[1]; S.pn[kPC + l][2] = pl[2]; S.pn[kPC + l][3] = pl[3];
-        S.plab[kPC + l] = lab;
-        S.clab[kPC + l] = lab;
+      // planes of the tetrahedra from `head` on in the queue, for one chain of
+      // reads (mesh, vertices) instead of one for each
+      if (late || head > pl1) {
+        pl0 = head - 1;
+        pl1 = late ? head : min(nt, pl0 + kTB);
+        const int e = pl0 + (l >> 2);
+        if (l < (late ? 4 : 4 * (pl1 - pl0))) {
+          const int b = late ? a : (e < kT ? S.tq[e] : GL(C.tq_spill)[spill + e - kT]);
+          double pl[4];
+          int lab;
+          tet_plane(D, X, b, l & 3, pl, lab);
+          S.pn[kPC + l][0] = pl[0]; S.pn[kPC + l][1] = pl[1]; S.pn[kPC + l][2] = pl[2]; S.pn[kPC + l][3] = pl[3];
+          S.plab[kPC + l] = lab;
+          S.clab[kPC + l] = lab;
+        }
+        lds_order();
       }
-      lds_order();
+      P = kPC + (late ? 0 : 4 * (head - 1 - pl0));
       uint64_t bad = 0;
       bool empty = false;
+      // (a plane that no corner of the cell is behind cuts nothing of it later)
+      unsigned todo = 0;
+      {
+        double g[4][4];
+#pragma unroll
+        for (int f = 0; f < 4; f++) {
+          const double2 *e = reinterpret_cast<const double2 *>(S.pn[P + f]);
+          const double2 e0 = e[0], e1 = e[1];
+          g[f][0] = e0.x; g[f][1] = e0.y; g[f][2] = e1.x; g[f][3] = e1.y;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < 4; f++) {
+          const uint64_t O = outside_of(Q, g[f], g[f][3]);
+          todo |= O ? 1u << f : 0u;
+          empty = empty | (O == Q.M);
+        }
+      }
+      if (empty) continue;
 #pragma unroll 1
-      for (int f = kPC; f < kP; f++) {
+      for (; todo; todo &= todo - 1) {
+        const int f = P + __ffs(todo) - 1;
         const double n[3] = {S.pn[f][0], S.pn[f][1], S.pn[f][2]}, c = S.pn[f][3];
         const uint64_t O = outside_of(Q, n, c);
         if (!O) continue;
@@ -779,7 +830,7 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
       // ---- emit the piece ----
       if (GRAD) {
         touched = touched | (LOOSE && loose) | (nwait == 64) |
-                  (lanes((l >= kPC) & (l < kP) & (S.plab[l < kP ? l : 0] <= VD_BND_BASE + 3)) & fmask) != 0;
+                  (lanes((l >= kPC) & (S.plab[l] <= VD_BND_BASE + 3)) & fmask) != 0;
         now = whole || touched;
       }
       if (!now) bis = 0;
@@ -843,8 +894,8 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     // ---- propagate: neighbours (cell planes), tetrahedra (the planes of T_a) ----
     nbmask |= fmask & cellpos;
     if (whole) break;
-    for (uint64_t m = fmask >> kPC; m; m &= m - 1) {
-      const int lab = uni(S.plab[kPC + __ffsll((unsigned long long)m) - 1]);
+    for (uint64_t m = fmask >> kPC << kPC; m; m &= m - 1) {
+      const int lab = uni(S.plab[__ffsll((unsigned long long)m) - 1]);
       if (lab > VD_BND_BASE + 3 && !push(-lab - 1)) { err = 2; where = VD_STAGE_SIMPLICES; break; }
     }
     lds_order();

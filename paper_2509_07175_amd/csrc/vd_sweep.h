@@ -54,9 +54,11 @@ __device__ __forceinline__ int wave_incl_max(int v) {
 // most 8 cells, sized from the density of the 3x3x3 block to hold about 2.5 kK
 // sites) by bucket of squared distance, in block order within a bucket (the
 // same on every run).  When more than kK are in the block, a prefix of buckets
-// that fits is kept.  Each candidate is read twice (64 a batch): once for its
-// bucket, once it has its place; the row of a candidate is the last row start at
-// or before it, a prefix maximum over LDS marks.
+// that fits is kept.  The row of a candidate is the last row start at or before
+// it, a prefix maximum over LDS marks; then all candidates (64 a batch) are read
+// together, for one wait, and stay in registers until they have their places
+// (read batch by batch, and again for their places: 5M uniform sites 53.5
+// against 52.1 ms).
 // Returns the number of sites held, or -1 (too dense: no copy).
 // ---------------------------------------------------------------------------
 template <bool POW, class L>
@@ -165,17 +167,32 @@ __device__ __forceinline__ int fill_sites(L &S, const GridView &G, double vx, do
 #pragma unroll
   for (int h = 0; h < kBatch; h++) {
     pos[h] = -1;
-    kb[h] = kNB;
     if (h < nbat) {
       const int t = 64 * h + l;
       const int row = max(wave_incl_max(S.R.row[t]), carry);
       carry = __builtin_amdgcn_readlane(row, 63);
-      if (t < total) {
-        const int p = S.R.base[row] + t;
-        pos[h] = p;
-        const double ax = GL(G.sx)[p] - vx, ay = GL(G.sy)[p] - vy, az = GL(G.sz)[p] - vz;
-        kb[h] = bucket(ax * ax + ay * ay + az * az);
-        __hip_atomic_fetch_or(&S.B.bits[h][kb[h]], 1ull << l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (t < total) pos[h] = S.R.base[row] + t;
+    }
+  }
+  // all reads of a group of batches in flight together
+  double ax[kBatch], ay[kBatch], az[kBatch];
+  auto read = [&](int h) {
+    const int p = pos[h] >= 0 ? pos[h] : 0;
+    ax[h] = GL(G.sx)[p]; ay[h] = GL(G.sy)[p]; az[h] = GL(G.sz)[p];
+  };
+  read(0); read(1); read(2); read(3);
+  if (nbat > 4) { read(4); read(5); }
+  if (nbat > 6) { read(6); read(7); }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int h = 0; h < kBatch; h++) {
+    kb[h] = kNB;
+    if (h < nbat) {
+      ax[h] -= vx; ay[h] -= vy; az[h] -= vz;
+      const int k = bucket(ax[h] * ax[h] + ay[h] * ay[h] + az[h] * az[h]);
+      if (pos[h] >= 0) {
+        kb[h] = k;
+        __hip_atomic_fetch_or(&S.B.bits[h][k], 1ull << l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
   }
@@ -208,7 +225,7 @@ __device__ __forceinline__ int fill_sites(L &S, const GridView &G, double vx, do
   for (int h = 0; h < kBatch; h++) {
     if (h < nbat && kb[h] < B) {
       const int p = pos[h];
-      const double n0 = GL(G.sx)[p] - vx, n1 = GL(G.sy)[p] - vy, n2 = GL(G.sz)[p] - vz;
+      const double n0 = ax[h], n1 = ay[h], n2 = az[h];
       double *e = S.K.s[rk[h]];
       e[0] = n0; e[1] = n1; e[2] = n2;
       e[3] = POW ? 0.5 * (n0 * n0 + n1 * n1 + n2 * n2 + w - GL(G.sw)[p]) : 0.5 * (n0 * n0 + n1 * n1 + n2 * n2);
