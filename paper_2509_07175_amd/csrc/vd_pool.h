@@ -5,9 +5,13 @@
 // local handles) pays about 50 allocations and as many frees for each, most of
 // the time of a small diagram.  Here a freed handle's blocks are kept and handed
 // to the next one of about the same size: forward and backward of 4,000 sites
-// through the autograd function 8.9 -> 2.5 ms (1.9 of it kernels).
+// through the autograd function 8.9 -> 2.5 ms when it came (0.8 now).
 //
-// Bounds: at most kPoolBytes are kept; nothing is when no handle of the library is
+// Bounds: at most kPoolBytes are kept.  Where they do not suffice, blocks that
+// kStale handles ended without taking make room (a program that changes its sizes
+// is not left with blocks that fit no more: Lloyd calls of 140,000 sites after
+// smaller ones 73 against 10 ms), and else the new ones are given back; nothing of
+// a handle larger than that is kept.  Nothing is when no handle of the library is
 // left; an allocation that fails gives all of it back and tries again.  A block
 // enters the pool only after one block of its handle went through hipFree, which
 // waits for the device: whatever ran on any stream with the handle's memory is
@@ -25,7 +29,8 @@
 
 class BlockPool {
  public:
-  static constexpr size_t kPoolBytes = 1ull << 30;  // 0.3 % of the card's memory
+  static constexpr size_t kPoolBytes = 4ull << 30;  // 1.4 % of the card's memory
+  static constexpr unsigned long long kStale = 8;
   static BlockPool &get() {
     static BlockPool *p = new BlockPool;  // (outlives handles that are freed at exit)
     return *p;
@@ -42,7 +47,7 @@ class BlockPool {
       auto &m = free_[{dev, host}];
       auto it = m.lower_bound(bytes);
       if (it != m.end() && it->first <= bytes + bytes / 4 + 4096) {
-        void *p = it->second;
+        void *p = it->second.p;
         live_[p] = {it->first, dev, host};
         kept_ -= it->first;
         m.erase(it);
@@ -82,10 +87,11 @@ class BlockPool {
 
   // the blocks of a handle that ends (`blocks`: device blocks first)
   void release(std::initializer_list<void *> blocks) {
+    const bool small = begin_release(blocks);
     bool idle = false;  // the device has been waited for
     for (void *p : blocks) {
       if (!p) continue;
-      if (!idle || !keep(p)) {
+      if (!idle || !small || !keep(p)) {
         const bool mine = on_current_device(p);
         const hipError_t e = free_now(p);
         idle = idle || (mine && e == hipSuccess);
@@ -118,7 +124,7 @@ class BlockPool {
     for (auto &m : out)
       for (auto &b : m.second) {
         any = true;
-        (void)(m.first.second ? hipHostFree(b.second) : hipFree(b.second));
+        give_back(b.second.p, m.first.second);
       }
     return any;
   }
@@ -129,6 +135,11 @@ class BlockPool {
     int dev;
     bool host;
   };
+  struct Kept {
+    void *p;
+    unsigned long long age;  // handles that had ended when it was kept
+  };
+  using Free = std::map<std::pair<int, bool>, std::multimap<size_t, Kept>>;  // by device and kind, then size
 
   static hipError_t raw_alloc(void **out, size_t bytes, bool host) {
     return host ? hipHostMalloc(out, bytes, hipHostMallocDefault) : hipMalloc(out, bytes);
@@ -140,24 +151,58 @@ class BlockPool {
     auto it = live_.find(p);
     return it != live_.end() && it->second.dev == dev && !it->second.host;
   }
+  static void give_back(void *p, bool host) { (void)(host ? hipHostFree(p) : hipFree(p)); }
+  // counts the handle; false: it is too large to be kept
+  bool begin_release(std::initializer_list<void *> blocks) {
+    std::lock_guard<std::mutex> lk(mu_);
+    clock_++;
+    size_t sum = 0;
+    for (void *p : blocks) {
+      auto it = live_.find(p);
+      if (it != live_.end()) sum += it->second.bytes;
+    }
+    return sum <= kPoolBytes;
+  }
   bool keep(void *p) try {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return false;
-    std::lock_guard<std::mutex> lk(mu_);
+    std::unique_lock<std::mutex> lk(mu_);
     auto it = live_.find(p);
-    if (it == live_.end() || it->second.dev != dev || kept_ + it->second.bytes > kPoolBytes) return false;
-    free_[{dev, it->second.host}].insert({it->second.bytes, p});
-    kept_ += it->second.bytes;
-    live_.erase(it);
+    if (it == live_.end() || it->second.dev != dev) return false;
+    const size_t bytes = it->second.bytes;
+    const bool host = it->second.host;
+    while (kept_ + bytes > kPoolBytes) {
+      // the oldest stale one (few blocks are ever kept: a search is enough)
+      Free::mapped_type *from = nullptr;
+      Free::mapped_type::iterator old;
+      bool old_host = false;
+      for (auto &m : free_)
+        for (auto b = m.second.begin(); b != m.second.end(); ++b)
+          if (b->second.age + kStale <= clock_ && (!from || b->second.age < old->second.age)) {
+            from = &m.second;
+            old = b;
+            old_host = m.first.second;
+          }
+      if (!from) return false;
+      void *q = old->second.p;
+      kept_ -= old->first;
+      from->erase(old);
+      lk.unlock();
+      give_back(q, old_host);
+      lk.lock();
+    }
+    free_[{dev, host}].insert({bytes, Kept{p, clock_}});
+    kept_ += bytes;
+    live_.erase(p);
     return true;
   } catch (const std::bad_alloc &) {
     return false;
   }
 
   std::mutex mu_;
-  using Free = std::map<std::pair<int, bool>, std::multimap<size_t, void *>>;  // by device and kind, then size
   Free free_;
   std::unordered_map<void *, Block> live_;
   size_t kept_ = 0;
+  unsigned long long clock_ = 0;
   long long handles_ = 0;
 };
