@@ -22,30 +22,30 @@ sys.path.insert(0, ROOT)
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # MI355X dense FP64 vector
 HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
 # algorithmic FP64 work per unit; every unit is counted on the device (vd_cells_info)
-FLOPS_PER_CANDIDATE = 8          # |q - s|^2 of one candidate site: 3 sub, 1 mul, 2 fma
-FLOPS_PER_CLASSIFIED = 6         # n.y - c of one corner against a clipping plane: 1 mul, 2 fma, 1 sub
+FLOPS_PER_TEST = 6               # n.y > c of one corner against a site's bisector: 1 mul, 2 fma, 1 compare
 FLOPS_PER_NEW_CORNER = 51        # Cramer solve of three planes: 3 cross products (27), det (5),
                                  # reciprocal (1), 3 coordinates (18)
-FLOPS_PER_FAN_TET = 78           # one moment-fan tetrahedron: plane foot (15), det (14), volume (1),
-                                 # corner sums (12), volume / first moment (10), energy (26)
+NEW_CORNERS_PER_CLIP = 5         # edges of a new face (5.2 on average for uniform sites)
+FLOPS_PER_MOMENT_TET = 54        # one tetrahedron of a piece's moments: det (14), corner sums (6),
+                                 # first moment (6), energy (28)
 # algorithmic HBM bytes, per counted unit
 BYTES_PER_SITE = 110 + 48        # inputs (site, sorted copy, perm, grid, simplices share) + per-site outputs
 BYTES_PER_PIECE = 72             # piece record
 BYTES_PER_FACE = 4               # face label
 BYTES_PER_VERT = 36              # vertex coordinates + 3 labels
 BYTES_PER_NBR = 8                # neighbour (arena + CSR)
-KERNEL_FILES = ("clip3d.hip", "vd_common.h", "vd_arena.h", "vd_internal.h")
+KERNEL_FILES = ("sweep3d.hip", "vd_sweep.h", "vd_site.h", "vd_common.h", "vd_arena.h", "vd_internal.h")
 
 
 def recorded_traffic():
-    """HBM bytes per site_kernel launch from the committed counter profile, if
+    """HBM bytes per sweep_kernel launch from the committed counter profile, if
     the kernel sources are still the profiled ones (else None)."""
     import hashlib
     h = hashlib.sha256()
     for f in KERNEL_FILES:
         with open(os.path.join(ROOT, "paper_2509_07175_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
-    path = os.path.join(ROOT, "profiles", "site_kernel_c3_counters.md")
+    path = os.path.join(ROOT, "profiles", "sweep_kernel_c3_counters.md")
     if not os.path.exists(path):
         return None
     rec = {}
@@ -535,9 +535,8 @@ def main():
     free_after, _ = torch.cuda.mem_get_info()
     info = cells.info()
     ms = 1e3 * wall / args.steps
-    # the work of the same step, counted by one more clip with the kernel's
-    # counters on (they cost time, so the timed steps run without them; the
-    # work is the same: identical inputs give identical queries and clips)
+    # the searched kernel's work on the same step (it takes a monitored clip), for
+    # the counters and the predicates' margins
     mopts = vd.Options.default(time_kernels=1, emit_polytopes=0 if args.no_emit else 1,
                                carve_mode=args.carve_mode, improved_search=args.improved,
                                use_straddle_edges=args.straddle, site_cache=args.site_cache, monitor=1)
@@ -545,10 +544,16 @@ def main():
     vd.clip_cells(grid, d, mopts, cells=mcells)
     minfo = mcells.info()
     del mcells
-    # the dominant kernel: the persistent per-site kernel (cell carve + pieces)
-    dom_ms, dom_name = float(np.mean(kern)), "site_kernel"
-    flops = (FLOPS_PER_CANDIDATE * minfo["candidates"] + FLOPS_PER_CLASSIFIED * minfo["corners_classified"] +
-             FLOPS_PER_NEW_CORNER * minfo["corners_created"] + FLOPS_PER_FAN_TET * minfo["fan_simplices"])
+    # the dominant kernel: the persistent per-site kernel (cell and pieces).  Every
+    # site it tests is tested against all corners of the cell (queries: final
+    # corners), and a piece of v corners is about 2 v - 14 tetrahedra.
+    dom_ms = float(np.mean(kern))
+    dom_name = "sweep_kernel"
+    if args.carve_mode != 1 or args.improved or args.straddle or not args.site_cache:
+        dom_name = "site_kernel"
+    flops = (FLOPS_PER_TEST * info["candidates"] * (info["nn_queries"] / n) +
+             FLOPS_PER_NEW_CORNER * NEW_CORNERS_PER_CLIP * info["clips"] +
+             FLOPS_PER_MOMENT_TET * max(0, 2 * info["n_verts"] - 14 * info["n_pieces"]))
     achieved = flops / (dom_ms * 1e-3) / 1e12
     alg_bytes = (BYTES_PER_SITE * n + BYTES_PER_PIECE * info["n_pieces"] + BYTES_PER_FACE * info["n_faces"] +
                  BYTES_PER_VERT * info["n_verts"] + BYTES_PER_NBR * info["n_nbrs"])

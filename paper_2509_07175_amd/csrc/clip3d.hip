@@ -1,5 +1,7 @@
 // clip3d.hip -- clipped Voronoi cells in a tetrahedral domain, one wavefront
-// per site.
+// per site, by the paper's searches: clips with search options other than the
+// defaults or with work counters, and the cells that the kernel of the default
+// clip (sweep3d.hip) leaves.
 //
 // Carving (shared by both modes) follows Alg. 1 / Alg. 3:
 //   * a corner is classified by the point-in-cell test (Sec. 4.1, Eq. 2): it is

@@ -1,4 +1,7 @@
-// surface.hip -- restricted Voronoi diagram on a triangle mesh (Alg. 4).
+// surface.hip -- restricted Voronoi diagram on a triangle mesh (Alg. 4) by the
+// paper's searches: clips with search options other than the defaults or with
+// work counters, triangles that meet many cells, and those that the kernel of the
+// default clip (sweep2d.hip) leaves; and the per-site sums and lists of both.
 //
 // One wavefront per triangle T_a.  The first site is the nearest site of the
 // triangle's centroid; further sites come from the positive edge flags of the
