@@ -99,7 +99,8 @@ struct Stats {
 
 // Vertex of three planes by Cramer's rule, planes taken in ascending flag order
 // so a vertex does not depend on the order in which its planes were created.
-__device__ __forceinline__ void solve3(const WaveLds &S, int a, int b, int c, double *y) {
+// Returns how far they fix it: 2 to kSure, 1 to kFair, or 0.
+__device__ __forceinline__ int solve3(const WaveLds &S, int a, int b, int c, double *y) {
   int q[3] = {a, b, c};
 #pragma unroll
   for (int i = 0; i < 3; i++)
@@ -114,11 +115,12 @@ __device__ __forceinline__ void solve3(const WaveLds &S, int a, int b, int c, do
   const double id = 1.0 / det;
 #pragma unroll
   for (int k = 0; k < 3; k++) y[k] = (n0[3] * c12[k] + n1[3] * c20[k] + n2[3] * c01[k]) * id;
+  return fixed_to(kSure, det, n0, n1, n2) ? 2 : (fixed_to(kFair, det, n0, n1, n2) ? 1 : 0);
 }
 
 // Drop planes that no corner references (keeps slot order).  Returns the new
 // plane count.
-__device__ int compact_planes(WaveLds &S, int npl, int nc) {
+__device__ __forceinline__ int compact_planes(WaveLds &S, int npl, int nc) {
   const int l = vd_lane();
   uint64_t used = 0;
   for (int s = l; s < nc; s += 64) {
@@ -166,7 +168,7 @@ __device__ int compact_planes(WaveLds &S, int npl, int nc) {
 // narrow instance (nc <= 64 on entry, the common case) keeps one slot per
 // lane and one 64-bit mask per set.
 template <bool MON, bool W>
-__device__ int clip_poly_w(WaveLds &S, int P, int pt, int &nc, int ps, int kcert) {
+__device__ __forceinline__ int clip_poly_w(WaveLds &S, int P, int pt, int &nc, int ps, int kcert) {
   constexpr int NH = W ? 2 : 1;
   // bit s of the 128-bit set (lo, hi); narrow: every index is below 64
   auto bit = [](uint64_t lo, uint64_t hi, int s) { return W ? bit128(lo, hi, s) : ((lo >> s) & 1ull) != 0; };
@@ -319,14 +321,40 @@ __device__ int clip_poly_w(WaveLds &S, int P, int pt, int &nc, int ps, int kcert
   }
   __syncthreads();
   // coordinates of the new corners, one per lane (a removed corner may own up
-  // to three of them)
-  for (int t = l; t < nnew; t += 64) {
-    const int ns = nsurv + t;
-    const int cp = S.cpl[ns];
-    double yy[3];
-    solve3(S, p8(cp, 0), p8(cp, 1), p8(cp, 2), yy);
-    nf = nf || !isfinite(yy[0] + yy[1] + yy[2]);
-    S.cy[ns][0] = yy[0]; S.cy[ns][1] = yy[1]; S.cy[ns][2] = yy[2];
+  // to three of them; their first planes are distinct, so 64 lanes suffice)
+  int fixed = 2;
+  double yy[3] = {0, 0, 0};
+  if (l < nnew) {
+    const int cp = S.cpl[nsurv + l];
+    fixed = solve3(S, p8(cp, 0), p8(cp, 1), p8(cp, 2), yy);
+  }
+  if (__ballot(fixed < 2)) {
+    // the ends of the cut edges (removed, kept)
+    __syncthreads();
+    int t = base;
+#pragma unroll
+    for (int h = 0; h < NH; h++)
+#pragma unroll
+      for (int e = 0; e < 3; e++)
+        if (em[h] & (1 << e)) {
+          S.byFirst[t] = (unsigned char)(l + 64 * h);
+          S.bySecond[t] = (unsigned char)p8(nb[h], e);
+          t++;
+        }
+    __syncthreads();
+    const int o = S.byFirst[l < nnew ? l : 0], s = S.bySecond[l < nnew ? l : 0];
+    auto at = [&](double v0, double v1, int k) {
+      const double x = __shfl(v0, k & 63, 64), z = W ? __shfl(v1, k & 63, 64) : 0.0;
+      return W && k > 63 ? z : x;
+    };
+    const double A[3] = {at(y[0][0], y[1][0], o), at(y[0][1], y[1][1], o), at(y[0][2], y[1][2], o)};
+    const double B[3] = {at(y[0][0], y[1][0], s), at(y[0][1], y[1][1], s), at(y[0][2], y[1][2], s)};
+    const double n[3] = {nx, ny, nz};
+    if (fixed < 2) keep_on_edge(A, B, n, c, fixed == 1, yy);
+  }
+  if (l < nnew) {
+    nf = !isfinite(yy[0] + yy[1] + yy[2]);
+    S.cy[nsurv + l][0] = yy[0]; S.cy[nsurv + l][1] = yy[1]; S.cy[nsurv + l][2] = yy[2];
   }
   __syncthreads();
   nc = nsurv + nnew;
@@ -375,7 +403,7 @@ struct CarveParams {
 // on it has a 4th coordinate between h_i and 0.  The clip plane is the power
 // plane n.y <= (|n|^2 + w_i - w_j)/2 (the lifted bisector on the hyperplane).
 template <bool MON, bool POW>
-__device__ int carve(WaveLds &S, const GridView &G, const CarveParams C, const SiteCtx &X, int &npl, int &nc,
+__device__ __forceinline__ int carve(WaveLds &S, const GridView &G, const CarveParams C, const SiteCtx &X, int &npl, int &nc,
                      Stats &st) {
   enum { PICK = 0, TEST, LAMBDA, SEARCH };
   const int l = vd_lane();
@@ -611,7 +639,7 @@ __device__ int carve(WaveLds &S, const GridView &G, const CarveParams C, const S
 // P <- T_a: 4 planes (face f opposite vertex f), 4 corners.  Lane l < 4
 // builds plane l and corner l; the fixed topology of a positively oriented
 // tetrahedron is packed in constants.
-__device__ void init_tet(WaveLds &S, const DomainView &D, const SiteCtx &X, int a, int tested) {
+__device__ __forceinline__ void init_tet(WaveLds &S, const DomainView &D, const SiteCtx &X, int a, int tested) {
   const int l = vd_lane();
   if (l < 4) {
     double pl[4];
@@ -651,7 +679,7 @@ __device__ __forceinline__ SavedCell saved_cell(const CellsDev &C) {
   return B;
 }
 
-__device__ void save_cell(WaveLds &S, const CellsDev &C, int npl, int nc) {
+__device__ __forceinline__ void save_cell(WaveLds &S, const CellsDev &C, int npl, int nc) {
   const int l = vd_lane();
   const SavedCell B = saved_cell(C);
   if (l < npl) {
@@ -668,7 +696,7 @@ __device__ void save_cell(WaveLds &S, const CellsDev &C, int npl, int nc) {
 
 // ... and start a piece from it: the cell plus the four planes of T_a in
 // slots npl .. npl+3 (not yet cut)
-__device__ void restore_cell(WaveLds &S, const CellsDev &C, int npl, int nc, const DomainView &D, const SiteCtx &X,
+__device__ __forceinline__ void restore_cell(WaveLds &S, const CellsDev &C, int npl, int nc, const DomainView &D, const SiteCtx &X,
                              int a) {
   const int l = vd_lane();
   const SavedCell B = saved_cell(C);
@@ -693,7 +721,7 @@ __device__ void restore_cell(WaveLds &S, const CellsDev &C, int npl, int nc, con
 }
 
 // the cell in LDS (npl <= kLF planes, nc <= kLC corners) over the cache
-__device__ void save_cell_lds(WaveLds &S, int npl, int nc) {
+__device__ __forceinline__ void save_cell_lds(WaveLds &S, int npl, int nc) {
   const int l = vd_lane();
   __syncthreads();
   double p4[4] = {0, 0, 0, 0};
@@ -716,7 +744,7 @@ __device__ void save_cell_lds(WaveLds &S, int npl, int nc) {
 
 // start a piece from the LDS cell: the cell plus the four planes of T_a in
 // slots npl .. npl+3 (not yet cut)
-__device__ void restore_cell_lds(WaveLds &S, int npl, int nc, const DomainView &D, const SiteCtx &X, int a) {
+__device__ __forceinline__ void restore_cell_lds(WaveLds &S, int npl, int nc, const DomainView &D, const SiteCtx &X, int a) {
   const int l = vd_lane();
   if (l < npl) {
     for (int k = 0; k < 4; k++) S.pn[l][k] = S.LC.pn[l][k];
@@ -739,7 +767,7 @@ __device__ void restore_cell_lds(WaveLds &S, int npl, int nc, const DomainView &
 }
 
 // P <- box [lo, hi] (planes x-,x+,y-,y+,z-,z+; corner (bx,by,bz) = 4bx+2by+bz)
-__device__ void init_box(WaveLds &S, const SiteCtx &X, const double *lo, const double *hi) {
+__device__ __forceinline__ void init_box(WaveLds &S, const SiteCtx &X, const double *lo, const double *hi) {
   const int l = vd_lane();
   if (l < 6) {
     const int ax = l >> 1, side = l & 1;
@@ -780,7 +808,7 @@ __device__ void init_box(WaveLds &S, const SiteCtx &X, const double *lo, const d
 // Strang and Fix (centroid -27/48, points (3/5,1/5,1/5) 25/48); with a density
 // every integrand carries it and one degree-5 rule takes all twelve.
 template <bool DENS>
-__device__ void face_moments(WaveLds &S, int nc, int npl, uint64_t fmask, const CellsDev &C, const GridView &G,
+__device__ __forceinline__ void face_moments(WaveLds &S, int nc, int npl, uint64_t fmask, const CellsDev &C, const GridView &G,
                              const SiteCtx &X, long long pidx) {
   const int l = vd_lane();
   __syncthreads();
@@ -946,7 +974,7 @@ __device__ __forceinline__ void merge_halves(double (*ex)[3], double &depth, int
 }
 
 template <bool MON>
-__device__ int gabriel_clips(WaveLds &S, const SiteCtx &X, int &npl, int &nc, Stats &st) {
+__device__ __forceinline__ int gabriel_clips(WaveLds &S, const SiteCtx &X, int &npl, int &nc, Stats &st) {
   const int l = vd_lane();
   const int cl = l & 31;  // this lane's candidate
   const bool upper = l >= 32;
@@ -1095,7 +1123,7 @@ __device__ __forceinline__ bool nb_push(WaveLds &S, const CellsDev &C, int &nnb,
 // The carve has one call site: the first job of a cell-first site is the cell.
 // ---------------------------------------------------------------------------
 template <bool MON, bool DENS, bool POW, bool CORNERS>
-__device__ void do_site(WaveLds &S, const GridView &G0, const DomainView &D0, const CellsDev &C, int si) {
+__device__ __forceinline__ void do_site(WaveLds &S, const GridView &G0, const DomainView &D0, const CellsDev &C, int si) {
   const int l = vd_lane();
   // The views are re-read from memory (scalar loads) in each piece iteration
   // rather than held in scalar registers across the whole site: the opaque

@@ -129,7 +129,7 @@ __device__ __forceinline__ void vertex_of(const double *n0, const double *n1, co
 // whose first plane is w and whose second is u.  Returns false, the polytope
 // unchanged, when there are too few edges for a face or too many for the free
 // lanes.  `bad` collects the lanes whose new corner is degenerate (the edges do
-// not form one loop, or planes without a common point).
+// not form one loop).
 __device__ __forceinline__ bool cut(SweepLds &S, Poly &Q, uint64_t O, int P, const double *n, double c, uint64_t &bad) {
   const int l = vd_lane();
   auto beyond = [&](int e) { return lanes((int)((O << ((Q.nb >> (8 * e)) & 63)) >> 32) < 0); };
@@ -162,13 +162,35 @@ __device__ __forceinline__ bool cut(SweepLds &S, Poly &Q, uint64_t O, int P, con
   nb = in_mask(keep & x1) ? (int)__builtin_amdgcn_perm(f1, nb, 0x03020400u) : nb;
   nb = in_mask(keep & x2) ? (int)__builtin_amdgcn_perm(f2, nb, 0x03040100u) : nb;
   Q.nb = nb;
+  const double c12[3] = {g1[1] * n[2] - g1[2] * n[1], g1[2] * n[0] - g1[0] * n[2], g1[0] * n[1] - g1[1] * n[0]};
+  const double det = g0[0] * c12[0] + g0[1] * c12[1] + g0[2] * c12[2];
+  const uint64_t fixed = lanes(fixed_to(kSure, det, g0, g1, n));
+  if (__builtin_expect((N & ~fixed) != 0, 0)) {
+    // rarely: the ends of the cut edges (here again, or they would be kept for this)
+    uint64_t Oc = O;
+    asm("" : "+s"(Oc));
+    auto past = [&](int e) { return Oc & ~lanes((int)((Oc << ((Q.nb >> (8 * e)) & 63)) >> 32) < 0); };
+    const uint64_t d0 = past(0), d1 = past(1), d2 = past(2);
+    if (in_mask(d0)) S.rec[mbcnt64(d0)] = l;
+    if (in_mask(d1)) S.rec[__popcll(d0) + mbcnt64(d1)] = l;
+    if (in_mask(d2)) S.rec[__popcll(d0) + __popcll(d1) + mbcnt64(d2)] = l;
+    lds_order();
+    const int o = S.rec[mbcnt64(~(Q.M & ~Oc)) & 63] & 63, s = ~(rec >> 16) & 63;
+    const double A[3] = {__shfl(Q.y0, o, 64), __shfl(Q.y1, o, 64), __shfl(Q.y2, o, 64)};
+    const double B[3] = {__shfl(Q.y0, s, 64), __shfl(Q.y1, s, 64), __shfl(Q.y2, s, 64)};
+    double T[3];
+    vertex_of(g0, g1, n, c, T[0], T[1], T[2]);
+    if (!in_mask(fixed)) keep_on_edge(A, B, n, c, fixed_to(kFair, det, g0, g1, n), T);
+    if (in_mask(N)) { Q.y0 = T[0]; Q.y1 = T[1]; Q.y2 = T[2]; }
+  } else if (in_mask(N)) {
+    vertex_of(g0, g1, n, c, Q.y0, Q.y1, Q.y2);
+  }
   bool wrong = false;
   if (in_mask(N)) {
     Q.nb = (int)(rec >> 16) | fw << 8 | su << 16;
     Q.cp = (int)(rec & 0xffff) | P << 16;
-    vertex_of(g0, g1, n, c, Q.y0, Q.y1, Q.y2);
     // two corners with the same first (second) plane: not a simple loop
-    wrong = (fu != 63 - l) | (sw != 63 - l) | !isfinite(Q.y0 + Q.y1 + Q.y2);
+    wrong = (fu != 63 - l) | (sw != 63 - l);
   }
   bad |= lanes(wrong);
   Q.M = keep | N;
@@ -313,10 +335,10 @@ __device__ __forceinline__ int sweep(SweepLds &S, const GridView &G, const SiteC
     if (P < 0) return 2;
     set_plane(S, P, n, c, S.K.p[k]);
     if (!cut(S, Q, O, P, n, c, bad)) return 2;
+    if (bad) return 3;
     st.clips++;
     k++;
   }
-  if (bad) return 3;
   st.cands += k;
   st.queries += __popcll(Q.M);
   return 0;
@@ -357,6 +379,7 @@ __device__ __forceinline__ int ask_grid(SweepLds &S, const GridView &G, const Si
   st.queries += __popcll(asked);
   st.grid += __popcll(asked);
   const uint64_t inside = lanes(in);
+  uint64_t fresh = 0;  // planes of this round
   for (uint64_t m = asked; m; m = uni64(m & (m - 1))) {
     cell.M = uni64(cell.M);
     free_planes = uni64(free_planes);
@@ -367,12 +390,18 @@ __device__ __forceinline__ int ask_grid(SweepLds &S, const GridView &G, const Si
     const int j = __builtin_amdgcn_readlane(kq, g);
     const uint64_t at = 1ull << __builtin_amdgcn_readlane(slot, g);
     if ((inside >> g) & 1ull) { ask &= ~at; continue; }
-    // a site that has clipped already (also for another corner of this round)
-    // is nearer by rounding only: the corner is inside (cells are closed)
-    if (lanes(l < kPC && S.plab[l < kPC ? l : 0] == j) & ~free_planes) { ask &= ~at; continue; }
     const double n[3] = {GL(G.sx)[j] - X.vx, GL(G.sy)[j] - X.vy, GL(G.sz)[j] - X.vz};
     const double nn = n[0] * n[0] + n[1] * n[1] + n[2] * n[2];
     const double c = POW ? 0.5 * (nn + X.w - GL(G.sw)[j]) : 0.5 * nn;
+    // a site that has clipped already is nearer by rounding only, and the corner
+    // is inside (cells are closed); or the site clipped for another corner of
+    // this round, and this one is gone as well or asked again
+    const uint64_t has = lanes(l < kPC && S.plab[l < kPC ? l : 0] == j) & ~free_planes;
+    if (has) {
+      if ((has & ~fresh) && (outside_of(Q, n, c + 1e-9 * nn) & at)) return 3;
+      ask &= ~at;
+      continue;
+    }
     const uint64_t O = outside_of(cell, n, c);
     if (!O) { ask &= ~at; continue; }
     if (O == cell.M) return 1;
@@ -381,6 +410,7 @@ __device__ __forceinline__ int ask_grid(SweepLds &S, const GridView &G, const Si
     set_plane(S, P, n, c, j);
     S.clab[P] = GL(G.perm)[j];
     cellpos |= 1ull << P;
+    fresh |= 1ull << P;
     uint64_t bad = 0;
     if (!cut(S, cell, O, P, n, c, bad)) return 2;
     if (bad) return 3;
