@@ -295,8 +295,7 @@ __device__ __forceinline__ int sweep(SweepLds &S, const GridView &G, const SiteC
       if (k >= check) {
         check = k + 8;
         // no site beyond twice the farthest corner is nearer to any corner than v_i
-        const float f = wave_fmax(in_mask(Q.M) ? (float)(Q.y0 * Q.y0 + Q.y1 * Q.y1 + Q.y2 * Q.y2) : 0.0f);
-        const double R2 = (double)f * (1.0 + 1e-6);
+        const double R2 = wave_bound(in_mask(Q.M) ? Q.y0 * Q.y0 + Q.y1 * Q.y1 + Q.y2 * Q.y2 : 0.0);
         double lim = 4.0 * R2;
         if (POW) {
           const double reach = sqrt_bound(R2) + sqrt_bound(R2 + h2);
@@ -356,15 +355,15 @@ __device__ __forceinline__ int ask_grid(SweepLds &S, const GridView &G, const Si
   const double h2 = POW ? X.h * X.h : 0.0;
   int slot = -1;
   {
-    float f = in_mask(ask) ? (float)(Q.y0 * Q.y0 + Q.y1 * Q.y1 + Q.y2 * Q.y2) : -1.0f;
+    int f = in_mask(ask) ? __double2hiint(Q.y0 * Q.y0 + Q.y1 * Q.y1 + Q.y2 * Q.y2) : -1;
 #pragma unroll 1
     for (int g = 0; g < 4; g++) {
-      const float top = wave_fmax(f);
-      const uint64_t at = lanes(f == top) & ask;
-      if (!at || uni(top < 0.0f)) break;
+      const int top = wave_imax(f);
+      if (top < 0) break;
+      const uint64_t at = lanes(f == top);
       const int s = __ffsll((unsigned long long)at) - 1;
       slot = grp == g ? s : slot;
-      f = l == s ? -1.0f : f;
+      f = l == s ? -1 : f;
     }
   }
   const int src = slot >= 0 ? slot : __ffsll((unsigned long long)ask) - 1;

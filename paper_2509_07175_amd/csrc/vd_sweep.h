@@ -26,16 +26,19 @@ __device__ __forceinline__ int mbcnt64(uint64_t m) {
 }
 __device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
-// maximum of floats over the wave, of which one at least is not negative (their
-// bits compare as integers)
-__device__ __forceinline__ float wave_fmax(float f) {
-  int v = __float_as_int(f);
+// maximum over the wave
+__device__ __forceinline__ int wave_imax(int v) {
   v = max(v, perm_i<VD_DPP_QUAD_XOR1>(v));
   v = max(v, perm_i<VD_DPP_QUAD_XOR2>(v));
   v = max(v, perm_i<VD_DPP_ROW_HALF_MIRROR>(v));
   v = max(v, perm_i<VD_DPP_ROW_MIRROR>(v));
-  return __int_as_float(max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-                            max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48))));
+  return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+             max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+// a bound of doubles over the wave, none negative, at most 1e-6 above the largest:
+// their upper halves compare as integers, over the whole range of sizes
+__device__ __forceinline__ double wave_bound(double v) {
+  return __hiloint2double(wave_imax(__double2hiint(v)) + 1, 0);
 }
 
 // inclusive prefix maximum of a non-negative int over the wave
