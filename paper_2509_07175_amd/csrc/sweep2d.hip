@@ -64,7 +64,7 @@ struct __align__(16) TriSweepLds {
 };
 
 struct SweepStats2 {
-  long long queries = 0, cands = 0, clips = 0;
+  long long queries = 0, clips = 0;
 };
 
 // sum over a row of 16 lanes, the same value in each of them
@@ -81,6 +81,14 @@ __device__ __forceinline__ double row_min(double v) {
   v = fmin(v, perm_d<VD_DPP_QUAD_XOR2>(v));
   v = fmin(v, perm_d<VD_DPP_ROW_HALF_MIRROR>(v));
   v = fmin(v, perm_d<VD_DPP_ROW_MIRROR>(v));
+  return v;
+}
+
+__device__ __forceinline__ int row_imin(int v) {
+  v = min(v, perm_i<VD_DPP_QUAD_XOR1>(v));
+  v = min(v, perm_i<VD_DPP_QUAD_XOR2>(v));
+  v = min(v, perm_i<VD_DPP_ROW_HALF_MIRROR>(v));
+  v = min(v, perm_i<VD_DPP_ROW_MIRROR>(v));
   return v;
 }
 
@@ -143,7 +151,10 @@ __device__ __forceinline__ bool do_tri(TriSweepLds &S, const GridView &G, const 
     sh[b] = in ? e[3] : 1e300;
   }
   SweepStats2 st;
-  // the site nearest to x (x uniform in the row): f = s.x - |s|^2 / 2 is largest
+  // the site nearest to x (x uniform in the row): f = s.x - |s|^2 / 2 is largest.
+  // Of equal ones the lowest slot: sites at the same point are neighbours in the
+  // copy, by index, so that the first of them has the cell in every triangle (the
+  // others none), as in surface.hip
   auto nearest = [&](double x0, double x1, double x2, double &fb, int &kb) {
     double nf = 1e300;
     int nk = 0;
@@ -157,8 +168,7 @@ __device__ __forceinline__ bool do_tri(TriSweepLds &S, const GridView &G, const 
       }
     }
     fb = row_min(nf);
-    const unsigned w = row_of(lanes(nf == fb));
-    kb = __builtin_amdgcn_ds_bpermute(4 * ((l & 48) + __ffs(w) - 1), nk);
+    kb = row_imin(nf == fb ? nk : kK);
   };
   // does the copy hold every site that could be nearer to x than f says?
   auto covered = [&](double x0, double x1, double x2, double f) {
@@ -194,7 +204,6 @@ __device__ __forceinline__ bool do_tri(TriSweepLds &S, const GridView &G, const 
     pend0 = uni64(S.seen[0]);
     pend1 = uni64(S.seen[1]);
     st.queries += 4;
-    st.cands += 4 * held;
   }
   unsigned npieces = 0, nfaces = 0, dropped = 0;
 #pragma unroll 1
