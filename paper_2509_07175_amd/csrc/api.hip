@@ -53,6 +53,18 @@ vd_status fail(vd_status s, const char *fmt, ...) {
                   "%s failed: %s (%s:%d)", #expr, hipGetErrorString(e_), __FILE__, __LINE__); \
   } while (0)
 
+// Frees a handle that a call has made and does not return: on every way out,
+// *out is still NULL.
+template <typename H>
+struct MadeHere {
+  H h;
+  H *out;
+  void (*free)(H);
+  ~MadeHere() {
+    if (!*out) free(h);
+  }
+};
+
 template <typename T>
 hipError_t ensure(T *&p, int64_t &cap, int64_t need) {
   if (need <= cap && p) return hipSuccess;
@@ -237,6 +249,7 @@ vd_status build_grid_impl(const double *sites, int64_t n, int nb, const int64_t 
   {
     int64_t tmp;
     if (G->cap_n < n) {
+      G->cap_n = 0;
       tmp = 0; if ((e = ensure(G->sx, tmp, n)) != hipSuccess) goto herr;
       tmp = 0; if ((e = ensure(G->sy, tmp, n)) != hipSuccess) goto herr;
       tmp = 0; if ((e = ensure(G->sz, tmp, n)) != hipSuccess) goto herr;
@@ -248,6 +261,7 @@ vd_status build_grid_impl(const double *sites, int64_t n, int nb, const int64_t 
       G->cap_n = n;
     }
     if (G->cap_cell < G->ncell) {
+      G->cap_cell = 0;
       tmp = 0; if ((e = ensure(G->cstart, tmp, G->ncell + 1)) != hipSuccess) goto herr;
       tmp = 0; if ((e = ensure(G->ccount, tmp, G->ncell)) != hipSuccess) goto herr;
       tmp = 0; if ((e = ensure(G->fill, tmp, G->ncell)) != hipSuccess) goto herr;
@@ -255,6 +269,7 @@ vd_status build_grid_impl(const double *sites, int64_t n, int nb, const int64_t 
       G->cap_cell = G->ncell;
     }
     if (G->cap_nb < nb) {
+      G->cap_nb = 0;
       tmp = 0; if ((e = ensure(G->geom, tmp, 9 * (int64_t)nb)) != hipSuccess) goto herr;
       tmp = 0; if ((e = ensure(G->d_site_off, tmp, nb + 1)) != hipSuccess) goto herr;
       tmp = 0; if ((e = ensure(G->d_cell_off, tmp, nb + 1)) != hipSuccess) goto herr;
@@ -288,6 +303,7 @@ vd_status build_grid_impl(const double *sites, int64_t n, int nb, const int64_t 
     }
     goto ok;
   herr:
+    G->n = 0;  // (arrays are missing: no clip takes it)
     return fin(fail(e == hipErrorOutOfMemory ? VD_ERR_OUT_OF_MEMORY : VD_ERR_HIP, "%s: %s", who, hipGetErrorString(e)));
   }
 ok:
@@ -388,14 +404,14 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
   hipStream_t st = as_stream(stream);
   vd_domain D = *out ? *out : new vd_domain_s();
   if (!*out) BlockPool::get().handle_made();
-  auto bail = [&](vd_status r) {
-    if (!*out) vd_domain_free(D);
-    return r;
-  };
+  const MadeHere<vd_domain> made{D, out, vd_domain_free};
+  D->staged = false;
+  D->bnd_ref_s = 0;  // (of another surface)
   const int k = simplex_dim + 1;
   if (D->m != m || D->nv != nv || D->dim != simplex_dim) {
     hipFree(D->verts); hipFree(D->simp); hipFree(D->adj);
     D->verts = nullptr; D->simp = nullptr; D->adj = nullptr;
+    D->m = 0;
     HIP_TRY(hipMalloc((void **)&D->verts, sizeof(double) * 3 * nv));
     HIP_TRY(hipMalloc((void **)&D->simp, sizeof(int) * k * m));
     HIP_TRY(hipMalloc((void **)&D->adj, sizeof(int) * k * m));
@@ -453,12 +469,12 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
   HIP_TRY(hipMemcpyAsync(hmeas.data(), measure, sizeof(double) * m, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipMemcpyAsync(hconv.data(), convex, sizeof(int) * nb, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
-  if (hflags[0]) return bail(fail(VD_ERR_INVALID_ARG, "%s: vertex or adjacency index out of range", who));
+  if (hflags[0]) return fail(VD_ERR_INVALID_ARG, "%s: vertex or adjacency index out of range", who);
   if (hflags[2])
-    return bail(fail(VD_ERR_INVALID_ARG, "%s: a face is shared by more than two simplices (non-manifold mesh)", who));
+    return fail(VD_ERR_INVALID_ARG, "%s: a face is shared by more than two simplices (non-manifold mesh)", who);
   if (hflags[1])
-    return bail(fail(VD_ERR_INVALID_ARG, simplex_dim == 3 ? "%s: a tetrahedron has non-positive volume"
-                                                          : "%s: a degenerate triangle", who));
+    return fail(VD_ERR_INVALID_ARG, simplex_dim == 3 ? "%s: a tetrahedron has non-positive volume"
+                                                          : "%s: a degenerate triangle", who);
   D->convex = hconv;
   D->all_convex = simplex_dim == 3 && std::all_of(hconv.begin(), hconv.end(), [](int c) { return c != 0; });
   double tot = 0;
@@ -488,7 +504,7 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
       D->loc_off[b + 1] = D->loc_off[b] + (int64_t)D->lg[3 * b] * D->lg[3 * b + 1] * D->lg[3 * b + 2];
     }
     const int64_t ncell = D->loc_off[nb];
-    if (ncell > (int64_t)INT_MAX / 2) return bail(fail(VD_ERR_INVALID_ARG, "%s: location grid too large", who));
+    if (ncell > (int64_t)INT_MAX / 2) return fail(VD_ERR_INVALID_ARG, "%s: location grid too large", who);
     D->ncell = ncell;
     HIP_TRY(hipMalloc((void **)&D->lgeom, sizeof(double) * 9 * nb));
     HIP_TRY(hipMalloc((void **)&D->d_lg, sizeof(int) * 3 * nb));
@@ -526,7 +542,7 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
     int nbt = 0;
     HIP_TRY(hipMemcpyAsync(&nbt, pos + 4 * m, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    if (nbt < 4) return bail(fail(VD_ERR_INVALID_ARG, "%s: the domain has no boundary surface", who));
+    if (nbt < 4) return fail(VD_ERR_INVALID_ARG, "%s: the domain has no boundary surface", who);
     HIP_TRY(tmp.get(tri, 3 * (int64_t)nbt));
     HIP_TRY(tmp.get(adjm1, 3 * (int64_t)nbt));
     HIP_TRY(tmp.get(boff_d, nb + 1));
@@ -540,9 +556,10 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
     HIP_TRY(hipStreamSynchronize(st));
     const vd_status r = domain_create_impl(D->verts, tri, adjm1, nb, D->vert_off.data(), boff.data(), 2, stream,
                                            &D->bnd, who);
-    if (r != VD_OK) return bail(r);
+    if (r != VD_OK) return r;
   }
   HIP_TRY(hipStreamSynchronize(st));
+  D->staged = true;
   *out = D;
   return VD_OK;
 }
@@ -608,8 +625,11 @@ struct Caps {
 hipError_t alloc_cells(vd_cells c, int64_t n, const Caps &want) {
   CellsDev &d = c->d;
   hipError_t e;
+  // (no capacity while its arrays are replaced: a growth that fails leaves some of
+  // them freed)
   if (c->cap_n < n) {
     int64_t t;
+    c->cap_n = 0;
     t = 0; if ((e = ensure(d.mass, t, n)) != hipSuccess) return e;
     t = 0; if ((e = ensure(d.mom, t, 3 * n)) != hipSuccess) return e;
     t = 0; if ((e = ensure(d.energy, t, n)) != hipSuccess) return e;
@@ -635,6 +655,7 @@ hipError_t alloc_cells(vd_cells c, int64_t n, const Caps &want) {
   int64_t cp = d.cap_piece;
   if (cp < want.piece) {
     int64_t t;
+    d.cap_piece = c->cap_pid = 0;
     t = 0; if ((e = ensure(d.piece_site, t, want.piece)) != hipSuccess) return e;
     t = 0; if ((e = ensure(d.piece_simplex, t, want.piece)) != hipSuccess) return e;
     t = 0; if ((e = ensure(d.piece_nface, t, want.piece)) != hipSuccess) return e;
@@ -653,6 +674,7 @@ hipError_t alloc_cells(vd_cells c, int64_t n, const Caps &want) {
   }
   if (d.cap_nbr < want.nbr) {
     int64_t t = 0;
+    d.cap_nbr = c->cap_nbr_csr = 0;
     if ((e = ensure(d.nbr_arena, t, want.nbr)) != hipSuccess) return e;
     t = 0;
     if ((e = ensure(c->nbr, t, want.nbr)) != hipSuccess) return e;
@@ -661,11 +683,13 @@ hipError_t alloc_cells(vd_cells c, int64_t n, const Caps &want) {
   }
   if (want.face > 0 && d.cap_face < want.face) {
     int64_t t = 0;
+    d.cap_face = 0;
     if ((e = ensure(d.face_label, t, want.face)) != hipSuccess) return e;
     d.cap_face = want.face;
   }
   if (want.vert > 0 && d.cap_vert < want.vert) {
     int64_t t = 0;
+    d.cap_vert = 0;
     if ((e = ensure(d.vert_xyz, t, 3 * want.vert)) != hipSuccess) return e;
     t = 0;
     if ((e = ensure(d.vert_label, t, 3 * want.vert)) != hipSuccess) return e;
@@ -673,6 +697,7 @@ hipError_t alloc_cells(vd_cells c, int64_t n, const Caps &want) {
   }
   if (want.fint > 0 && d.cap_fint < want.fint) {
     int64_t t = 0;
+    d.cap_fint = 0;
     if ((e = ensure(d.fint, t, 12 * want.fint)) != hipSuccess) return e;
     t = 0;
     if ((e = ensure(d.fint_lab, t, want.fint)) != hipSuccess) return e;
@@ -797,6 +822,8 @@ vd_status boundary_for_clip(vd_domain dom, int64_t n, void *stream, vd_domain &b
 
 vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void *stream, vd_cells *out) {
   if (!out || !g || !dom) return fail(VD_ERR_INVALID_ARG, "vd_clip_cells: NULL handle");
+  if (g->n < 1) return fail(VD_ERR_INVALID_ARG, "vd_clip_cells: the grid's last build failed");
+  if (!dom->staged) return fail(VD_ERR_INVALID_ARG, "vd_clip_cells: the domain's last vd_domain_create failed");
   if (g->nb != dom->nb)
     return fail(VD_ERR_INVALID_ARG, "vd_clip_cells: the grid holds %d diagram(s), the domain %d", g->nb, dom->nb);
   if (opt_in && opt_in->no_sync) {
@@ -839,10 +866,7 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
   c->dim = dom->dim;
   c->opt = opt;
   c->grid = g;
-  auto bail = [&](vd_status r) {
-    if (!*out) vd_cells_free(c);
-    return r;
-  };
+  const MadeHere<vd_cells> made{c, out, vd_cells_free};
   Caps want;
   // first sizes.  n convex cells and m simplices that overlay each other meet in
   // about n + m + 6 (n^2/3 m^1/3 + n^1/3 m^2/3) pieces (the two cross terms come
@@ -875,9 +899,10 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
   }
   for (int attempt = 0; attempt < 8; attempt++) {
     hipError_t e = alloc_cells(c, n, want);
-    if (e != hipSuccess)
-      return bail(fail(e == hipErrorOutOfMemory ? VD_ERR_OUT_OF_MEMORY : VD_ERR_HIP, "vd_clip_cells: %s",
-                       hipGetErrorString(e)));
+    if (e != hipSuccess) {
+      c->status = e == hipErrorOutOfMemory ? VD_ERR_OUT_OF_MEMORY : VD_ERR_HIP;
+      return fail((vd_status)c->status, "vd_clip_cells: %s", hipGetErrorString(e));
+    }
     CellsDev &d = c->d;
     d.n = (int)n;
     d.emit = opt.emit_polytopes ? 1 : 0;
@@ -914,9 +939,10 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     const int wgs = dom->dim == 3 ? std::max(vd_sweep_workgroups(n), wgen) : 0;
     if (dom->dim == 3 &&
         (c->cap_spill < wgs || d.q_spill < c->q_spill_want || d.nbs_cap < c->nb_spill_want)) {
-      if (opt.no_sync) return bail(fail(VD_ERR_INVALID_ARG, "vd_clip_cells: no_sync on an unsized handle"));
+      if (opt.no_sync) return fail(VD_ERR_INVALID_ARG, "vd_clip_cells: no_sync on an unsized handle");
       const int64_t w = std::max<int64_t>(wgs, c->cap_spill);
       c->cap_gen = std::max<int64_t>(wgen, c->cap_gen);
+      c->cap_spill = 0;
       int64_t t = 0;
       HIP_TRY(ensure(d.tq_spill, t, w * (c->q_spill_want + VD_Q_MAX)));
       t = 0;
@@ -985,12 +1011,12 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
         HIP_TRY(hipMemcpyAsync(ho, c->outside, sizeof ho, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         if (ho[4] > 0)
-          return bail(fail(VD_ERR_INVALID_ARG, "vd_clip_cells: %d site(s) with a coordinate that is not finite "
-                                               "(first: %d)", ho[4], ho[5]));
+          return fail(VD_ERR_INVALID_ARG, "vd_clip_cells: %d site(s) with a coordinate that is not finite "
+                                               "(first: %d)", ho[4], ho[5]);
         // Eq. 1 needs distinct sites: a copy of a site has no cell of its own
         if (ho[2] > 0)
-          return bail(fail(VD_ERR_INVALID_ARG, "vd_clip_cells: %d site(s) repeat an earlier site exactly (first: %d)",
-                           ho[2], ho[3]));
+          return fail(VD_ERR_INVALID_ARG, "vd_clip_cells: %d site(s) repeat an earlier site exactly (first: %d)",
+                           ho[2], ho[3]);
         if (opt.boundary_seeds != 0) {
           c->sites_outside = ho[0];
           use_b = opt.boundary_seeds == 1 || !dom->all_convex || ho[0] > 0;
@@ -1008,12 +1034,12 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
       }
       d.whole = !opt.whole_interior ? 0 : (use_b ? 1 : 2);
       if (use_b) {
-        if (!dom->bnd) return bail(fail(VD_ERR_INVALID_ARG, "vd_clip_cells: the domain has no boundary surface"));
+        if (!dom->bnd) return fail(VD_ERR_INVALID_ARG, "vd_clip_cells: the domain has no boundary surface");
         vd_domain bd = nullptr;
         const int *btet = nullptr;
         {
           const vd_status r = boundary_for_clip(dom, n, stream, bd, btet);
-          if (r != VD_OK) return bail(r);
+          if (r != VD_OK) return r;
         }
         vd_options bopt;
         vd_options_default(&bopt);
@@ -1021,7 +1047,7 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
         bopt.max_search_iters = opt.max_search_iters;
         bopt.site_cache = opt.site_cache;
         const vd_status r = vd_clip_cells(g, bd, &bopt, stream, &c->bcells);
-        if (r != VD_OK) return bail(r);
+        if (r != VD_OK) return r;
         d.bseed_off = c->bcells->piece_off;
         d.bseed_pid = c->bcells->piece_id;
         d.bseed_tri = c->bcells->d.piece_simplex;
@@ -1151,7 +1177,7 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     *out = c;
     return VD_OK;
   }
-  return bail(fail(VD_ERR_HIP, "vd_clip_cells: output arenas kept overflowing"));
+  return fail(VD_ERR_HIP, "vd_clip_cells: output arenas kept overflowing");
 }
 
 void vd_cells_free(vd_cells c) {

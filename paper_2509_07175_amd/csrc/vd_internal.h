@@ -143,6 +143,7 @@ struct vd_domain_s {
   vd_domain_s *bnd_ref = nullptr;
   int *btet_ref = nullptr;
   int bnd_ref_s = 0;
+  bool staged = false;  // the last vd_domain_create succeeded
   // batch of nb domains (nb = 1: plain)
   int nb = 1;
   std::vector<int64_t> vert_off, simp_off, loc_off;  // host [nb + 1]

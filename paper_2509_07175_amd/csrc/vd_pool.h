@@ -56,10 +56,7 @@ class BlockPool {
       }
     }
     hipError_t e = raw_alloc(out, bytes, host);
-    if (e == hipErrorOutOfMemory && drain()) {
-      (void)hipGetLastError();
-      e = raw_alloc(out, bytes, host);
-    }
+    if (e == hipErrorOutOfMemory && drain()) e = raw_alloc(out, bytes, host);
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lk(mu_);
     live_[*out] = {bytes, dev, host};
@@ -142,7 +139,12 @@ class BlockPool {
   using Free = std::map<std::pair<int, bool>, std::multimap<size_t, Kept>>;  // by device and kind, then size
 
   static hipError_t raw_alloc(void **out, size_t bytes, bool host) {
-    return host ? hipHostMalloc(out, bytes, hipHostMallocDefault) : hipMalloc(out, bytes);
+    const hipError_t e = host ? hipHostMalloc(out, bytes, hipHostMallocDefault) : hipMalloc(out, bytes);
+    if (e != hipSuccess) {
+      *out = nullptr;
+      (void)hipGetLastError();  // (returned here: no later call is to find it)
+    }
+    return e;
   }
   bool on_current_device(void *p) {
     int dev = 0;

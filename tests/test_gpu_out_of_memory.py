@@ -1,0 +1,103 @@
+"""Device memory runs out in the middle of a call: the call reports it, what it
+had made is freed, and handles that were passed in stay usable."""
+import gc
+
+import numpy as np
+import pytest
+
+import vdgen
+from gpu_util import log
+
+pytestmark = pytest.mark.gpu
+
+OUT_OF_MEMORY = 2
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2509_07175_amd as vd
+    vd.load()
+    gc.collect()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+
+
+def _free():
+    import torch
+    gc.collect()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+def _fill(leave):
+    """Takes the device's memory but for about `leave` bytes (in steps: large
+    blocks leave some behind)."""
+    import torch
+    out = []
+    for _ in range(4):
+        n = torch.cuda.mem_get_info()[0] - leave
+        if n > 8 << 20:
+            out.append(torch.empty(n, dtype=torch.uint8, device="cuda"))
+    log(f"left {torch.cuda.mem_get_info()[0]}")
+    return out
+
+
+def _sites(n, seed=1):
+    import torch
+    return torch.as_tensor(vdgen.uniform_cube_sites(n, seed=seed, jitter=1e-7), device="cuda")
+
+
+def _mesh(k):
+    """A mesh's arrays on the device."""
+    import torch
+    d = vdgen.kuhn_cube_grid(k)
+    return (torch.as_tensor(d.verts, device="cuda"), torch.as_tensor(d.simplices.astype(np.int32), device="cuda"),
+            torch.as_tensor(d.adj.astype(np.int32), device="cuda"), 3)
+
+
+def test_a_domain_that_does_not_fit_leaves_nothing_behind():
+    import paper_2509_07175_amd as vd
+    dom = vd.Domain.from_vdgen(vdgen.kuhn_cube_grid(2))
+    g = vd.build_grid(_sites(2000), bbox=(0, 0, 0, 1, 1, 1))
+    vd.clip_cells(g, dom)
+    del g, dom
+    big = _mesh(80)  # 3 M tetrahedra: 49 MB each of indices and adjacency, and three times that besides
+    base = _free()
+    filler = _fill(32 << 20)
+    with pytest.raises(vd.VDError) as e:
+        vd.Domain(*big)
+    assert e.value.status == OUT_OF_MEMORY
+    del filler, e
+    # a handle made and freed: with no other left, the pool is given back as well
+    g = vd.build_grid(_sites(200000), bbox=(0, 0, 0, 1, 1, 1))
+    del g
+    lost = base - _free()
+    log(f"lost {lost}")
+    assert lost < 4 << 20
+
+
+def test_a_clip_that_does_not_fit_leaves_its_handles_usable():
+    import torch
+    import paper_2509_07175_amd as vd
+    dom = vd.Domain.from_vdgen(vdgen.kuhn_cube_grid(4))
+    small, large = _sites(3000), _sites(1000000, 2)
+    grid, cells = vd.Grid(), vd.Cells()
+    vd.build_grid(small, bbox=(0, 0, 0, 1, 1, 1), grid=grid)
+    ref = [t.clone() for t in vd.clip_cells(grid, dom, cells=cells).moments()]
+    filler = _fill(1 << 30)
+    vd.build_grid(large, bbox=(0, 0, 0, 1, 1, 1), grid=grid)
+    with pytest.raises(vd.VDError) as e:
+        vd.clip_cells(grid, dom, cells=cells)
+    assert e.value.status == OUT_OF_MEMORY
+    del filler, e
+    _free()
+    vd.build_grid(small, bbox=(0, 0, 0, 1, 1, 1), grid=grid)
+    got = vd.clip_cells(grid, dom, cells=cells).moments()
+    assert all(torch.equal(a, b) for a, b in zip(ref, got))
+    vd.build_grid(large, bbox=(0, 0, 0, 1, 1, 1), grid=grid)
+    m, _, _ = vd.clip_cells(grid, dom, cells=cells).moments()
+    assert abs(float(m.sum()) - 1.0) < 1e-11
