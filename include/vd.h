@@ -30,6 +30,10 @@
  *  - Handles own their device memory and keep it between calls: passing an
  *    existing handle back in (*out != NULL) reuses its buffers when they are
  *    large enough, so a steady-state loop performs no allocation.
+ *  - The buffers of freed grid and clip handles are kept for the next ones, up
+ *    to 4 GiB of device memory, until the last handle of the library (domains
+ *    included) is freed, an allocation of the library fails, or
+ *    vd_release_memory is called.
  */
 #ifndef VD_H
 #define VD_H
@@ -161,6 +165,10 @@ const char *vd_status_string(vd_status s);
  * error (a fault or a failed launch) as VD_ERR_HIP.  Errors of enqueued clips
  * (capacity, degeneracy, arena overflow) are reported by vd_cells_info. */
 vd_status vd_sync(void *stream);
+
+/* Gives the device memory kept from freed handles back (see above), for other
+ * allocations of the program.  Handles that are alive keep theirs. */
+vd_status vd_release_memory(void);
 
 /* ---------------------------------------------------------------------
  * vd_build_grid -- uniform grid over the sites for nearest-site queries

@@ -19,7 +19,7 @@ import os
 import numpy as np
 
 __all__ = ["load", "Options", "Grid", "Domain", "Cells", "build_grid", "clip_cells", "lloyd", "cvt_lbfgs",
-           "VoronoiMoments", "VDError", "BOUNDARY_BASE", "sync"]
+           "VoronoiMoments", "VDError", "BOUNDARY_BASE", "sync", "release_memory"]
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libvd.so")
@@ -139,6 +139,7 @@ def load():
         "vd_cell_moments": (C.c_int, [vp, vp, vp, vp, vp]),
         "vd_cell_moments_backward": (C.c_int, [vp, vp, vp, vp, vp, vp]),
         "vd_sync": (C.c_int, [vp]),
+        "vd_release_memory": (C.c_int, []),
         "vd_grid_set_weights": (C.c_int, [vp, vp, vp]),
         "vd_cell_moments_backward_noalloc": (C.c_int, [vp, vp, vp, vp, vp, vp]),
         "vd_domain_info": (C.c_int, [vp, C.POINTER(_DomainInfo)]),
@@ -156,12 +157,18 @@ def exported_symbols():
     return ["vd_options_default", "vd_last_error", "vd_status_string", "vd_build_grid", "vd_grid_free",
             "vd_build_grid_batch", "vd_domain_create_batch", "vd_domain_create", "vd_domain_free", "vd_clip_cells", "vd_cells_free", "vd_cells_info",
             "vd_cells_view", "vd_cell_moments", "vd_cell_moments_backward", "vd_sync", "vd_domain_info",
-            "vd_domain_adjacency", "vd_cell_moments_backward_noalloc", "vd_grid_set_weights"]
+            "vd_domain_adjacency", "vd_cell_moments_backward_noalloc", "vd_grid_set_weights",
+            "vd_release_memory"]
 
 
 def sync(stream=None):
     """vd_sync: waits for the stream's work and reports an asynchronous device error."""
     _check(load().vd_sync(_stream_ptr(stream)))
+
+
+def release_memory():
+    """vd_release_memory: gives the device memory kept from freed handles back."""
+    _check(load().vd_release_memory())
 
 
 def _check(status: int):

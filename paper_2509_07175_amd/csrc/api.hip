@@ -153,6 +153,8 @@ hipError_t upload_if_changed(T *dev, const T *host, size_t count, std::vector<T>
   return hipMemcpyAsync(dev, shadow.data(), sizeof(T) * count, hipMemcpyHostToDevice, st);
 }
 
+hipError_t device_alloc(void **out, size_t bytes) { return BlockPool::get().alloc_apart(out, bytes); }
+
 // device temporaries of one call, freed when it returns (on every path)
 struct TmpBuffers {
   std::vector<void *> p;
@@ -160,7 +162,7 @@ struct TmpBuffers {
   template <typename T>
   hipError_t get(T *&out, int64_t n) {
     out = nullptr;
-    const hipError_t e = hipMalloc((void **)&out, sizeof(T) * (size_t)std::max<int64_t>(n, 1));
+    const hipError_t e = device_alloc((void **)&out, sizeof(T) * (size_t)std::max<int64_t>(n, 1));
     if (e == hipSuccess) p.push_back(out);
     return e;
   }
@@ -412,17 +414,17 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
     hipFree(D->verts); hipFree(D->simp); hipFree(D->adj);
     D->verts = nullptr; D->simp = nullptr; D->adj = nullptr;
     D->m = 0;
-    HIP_TRY(hipMalloc((void **)&D->verts, sizeof(double) * 3 * nv));
-    HIP_TRY(hipMalloc((void **)&D->simp, sizeof(int) * k * m));
-    HIP_TRY(hipMalloc((void **)&D->adj, sizeof(int) * k * m));
+    HIP_TRY(device_alloc((void **)&D->verts, sizeof(double) * 3 * nv));
+    HIP_TRY(device_alloc((void **)&D->simp, sizeof(int) * k * m));
+    HIP_TRY(device_alloc((void **)&D->adj, sizeof(int) * k * m));
   }
   D->m = m; D->nv = nv; D->dim = simplex_dim; D->nb = nb;
   D->vert_off.assign(vert_off_host, vert_off_host + nb + 1);
   D->simp_off.assign(simp_off_host, simp_off_host + nb + 1);
   hipFree(D->d_simp_off); hipFree(D->d_vert_off); hipFree(D->d_loc_off); hipFree(D->d_lg); hipFree(D->d_views);
   D->d_simp_off = D->d_vert_off = D->d_loc_off = nullptr; D->d_lg = nullptr; D->d_views = nullptr;
-  HIP_TRY(hipMalloc((void **)&D->d_simp_off, sizeof(long long) * (nb + 1)));
-  HIP_TRY(hipMalloc((void **)&D->d_vert_off, sizeof(long long) * (nb + 1)));
+  HIP_TRY(device_alloc((void **)&D->d_simp_off, sizeof(long long) * (nb + 1)));
+  HIP_TRY(device_alloc((void **)&D->d_vert_off, sizeof(long long) * (nb + 1)));
   HIP_TRY(hipMemcpy(D->d_simp_off, D->simp_off.data(), sizeof(long long) * (nb + 1), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(D->d_vert_off, D->vert_off.data(), sizeof(long long) * (nb + 1), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpyAsync(D->verts, verts, sizeof(double) * 3 * nv, hipMemcpyDeviceToDevice, st));
@@ -506,13 +508,13 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
     const int64_t ncell = D->loc_off[nb];
     if (ncell > (int64_t)INT_MAX / 2) return fail(VD_ERR_INVALID_ARG, "%s: location grid too large", who);
     D->ncell = ncell;
-    HIP_TRY(hipMalloc((void **)&D->lgeom, sizeof(double) * 9 * nb));
-    HIP_TRY(hipMalloc((void **)&D->d_lg, sizeof(int) * 3 * nb));
-    HIP_TRY(hipMalloc((void **)&D->d_loc_off, sizeof(long long) * (nb + 1)));
-    HIP_TRY(hipMalloc((void **)&D->lstart, sizeof(int) * (ncell + 1)));
-    HIP_TRY(hipMalloc((void **)&D->lcount, sizeof(int) * ncell));
-    HIP_TRY(hipMalloc((void **)&D->lfill, sizeof(int) * ncell));
-    HIP_TRY(hipMalloc((void **)&D->scan_tmp, sizeof(int) * (ncell / 1024 + 2)));
+    HIP_TRY(device_alloc((void **)&D->lgeom, sizeof(double) * 9 * nb));
+    HIP_TRY(device_alloc((void **)&D->d_lg, sizeof(int) * 3 * nb));
+    HIP_TRY(device_alloc((void **)&D->d_loc_off, sizeof(long long) * (nb + 1)));
+    HIP_TRY(device_alloc((void **)&D->lstart, sizeof(int) * (ncell + 1)));
+    HIP_TRY(device_alloc((void **)&D->lcount, sizeof(int) * ncell));
+    HIP_TRY(device_alloc((void **)&D->lfill, sizeof(int) * ncell));
+    HIP_TRY(device_alloc((void **)&D->scan_tmp, sizeof(int) * (ncell / 1024 + 2)));
     HIP_TRY(hipMemcpy(D->lgeom, geom.data(), sizeof(double) * 9 * nb, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(D->d_lg, D->lg.data(), sizeof(int) * 3 * nb, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(D->d_loc_off, D->loc_off.data(), sizeof(long long) * (nb + 1), hipMemcpyHostToDevice));
@@ -521,13 +523,13 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
     HIP_TRY(hipMemcpyAsync(&total, D->lstart + ncell, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     D->nitems = total;
-    HIP_TRY(hipMalloc((void **)&D->litems, sizeof(int) * std::max(total, 1)));
+    HIP_TRY(device_alloc((void **)&D->litems, sizeof(int) * std::max(total, 1)));
     vd_launch_domain_fill(D, st);
   }
   {
     std::vector<DomainView> v(nb);
     for (int b = 0; b < nb; b++) v[b] = D->view_of(b);
-    HIP_TRY(hipMalloc((void **)&D->d_views, sizeof(DomainView) * nb));
+    HIP_TRY(device_alloc((void **)&D->d_views, sizeof(DomainView) * nb));
     HIP_TRY(hipMemcpy(D->d_views, v.data(), sizeof(DomainView) * nb, hipMemcpyHostToDevice));
   }
   if (simplex_dim == 3) {
@@ -548,7 +550,7 @@ vd_status domain_create_impl(const double *verts, const int32_t *simplices, cons
     HIP_TRY(tmp.get(boff_d, nb + 1));
     hipFree(D->btet);
     D->btet = nullptr;
-    HIP_TRY(hipMalloc((void **)&D->btet, sizeof(int) * nbt));
+    HIP_TRY(device_alloc((void **)&D->btet, sizeof(int) * nbt));
     vd_launch_fill_int(adjm1, 3 * (int64_t)nbt, -1, st);
     vd_launch_boundary_extract(D, pos, tri, D->btet, boff_d, st);
     std::vector<int64_t> boff((size_t)nb + 1);
@@ -580,6 +582,11 @@ vd_status vd_domain_create_batch(const double *verts, const int32_t *simplices, 
     return fail(VD_ERR_INVALID_ARG, "vd_domain_create_batch: missing batch or offsets");
   return domain_create_impl(verts, simplices, adjacency, batch->num, batch->vert_off, batch->simp_off, simplex_dim,
                             stream, out, "vd_domain_create_batch");
+}
+
+vd_status vd_release_memory(void) {
+  BlockPool::get().drain();
+  return VD_OK;
 }
 
 vd_status vd_domain_info(vd_domain D, vd_domain_info_t *info) {
@@ -800,7 +807,7 @@ vd_status boundary_for_clip(vd_domain dom, int64_t n, void *stream, vd_domain &b
     hipFree(dom->btet_ref);
     dom->btet_ref = nullptr;
     dom->bnd_ref_s = 0;
-    HIP_TRY(hipMalloc((void **)&dom->btet_ref, sizeof(int) * mr));
+    HIP_TRY(device_alloc((void **)&dom->btet_ref, sizeof(int) * mr));
     vd_launch_refine_triangles(bd, dom->btet, s, ov, otri, oadj, dom->btet_ref, st);
     HIP_TRY(hipGetLastError());
     std::vector<int64_t> so(bd->nb + 1), vo(bd->nb + 1);

@@ -12,7 +12,8 @@
 // is not left with blocks that fit no more: Lloyd calls of 140,000 sites after
 // smaller ones 73 against 10 ms), and else the new ones are given back; nothing of
 // a handle larger than that is kept.  Nothing is when no handle of the library is
-// left; an allocation that fails gives all of it back and tries again.  A block
+// left; an allocation of the library that fails gives all of it back and tries
+// again, and vd_release_memory does for the program's own.  A block
 // enters the pool only after one block of its handle went through hipFree, which
 // waits for the device: whatever ran on any stream with the handle's memory is
 // over.  When that call fails (a capture is running) or another device is
@@ -65,6 +66,13 @@ class BlockPool {
     if (*out) (void)(host ? hipHostFree(*out) : hipFree(*out));
     *out = nullptr;
     return hipErrorOutOfMemory;
+  }
+
+  // a device block that is not pooled
+  hipError_t alloc_apart(void **out, size_t bytes) {
+    hipError_t e = raw_alloc(out, bytes, false);
+    if (e == hipErrorOutOfMemory && drain()) e = raw_alloc(out, bytes, false);
+    return e;
   }
 
   // gives one block back to the device

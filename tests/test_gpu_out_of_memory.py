@@ -1,5 +1,6 @@
 """Device memory runs out in the middle of a call: the call reports it, what it
-had made is freed, and handles that were passed in stay usable."""
+had made is freed, handles that were passed in stay usable, and blocks kept from
+freed handles are given back before an allocation fails."""
 import gc
 
 import numpy as np
@@ -101,3 +102,35 @@ def test_a_clip_that_does_not_fit_leaves_its_handles_usable():
     vd.build_grid(large, bbox=(0, 0, 0, 1, 1, 1), grid=grid)
     m, _, _ = vd.clip_cells(grid, dom, cells=cells).moments()
     assert abs(float(m.sum()) - 1.0) < 1e-11
+
+
+def test_kept_blocks_make_room_for_a_domain():
+    import paper_2509_07175_amd as vd
+    keep = vd.Domain.from_vdgen(vdgen.kuhn_cube_grid(2))  # a live handle: the pool stays
+    g = vd.build_grid(_sites(300000), bbox=(0, 0, 0, 1, 1, 1))
+    c = vd.clip_cells(g, keep)
+    del g, c
+    big = _mesh(80)
+    _free()
+    filler = _fill(32 << 20)
+    d = vd.Domain(*big)  # fits in what the freed handles left
+    del filler
+    assert abs(d.info()["measure"] - 1.0) < 1e-9
+    del d, keep
+
+
+def test_kept_blocks_are_given_back_on_demand():
+    import paper_2509_07175_amd as vd
+    keep = vd.Domain.from_vdgen(vdgen.kuhn_cube_grid(2))
+    for _ in range(2):  # (the first clip leaves the runtime's scratch memory behind)
+        vd.release_memory()
+        base = _free()
+        g = vd.build_grid(_sites(300000), bbox=(0, 0, 0, 1, 1, 1))
+        c = vd.clip_cells(g, keep)
+        del g, c
+    held = base - _free()
+    vd.release_memory()
+    left = base - _free()
+    log(f"kept {held}, after release {left}")
+    assert held > 1 << 28 and left < 4 << 20
+    del keep
