@@ -875,13 +875,17 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
   c->grid = g;
   const MadeHere<vd_cells> made{c, out, vd_cells_free};
   Caps want;
-  // first sizes.  n convex cells and m simplices that overlay each other meet in
-  // about n + m + 6 (n^2/3 m^1/3 + n^1/3 m^2/3) pieces (the two cross terms come
-  // from cells crossing simplex faces and simplices crossing cell faces; 5.4 to
-  // 5.7 was measured on uniform sites); of their faces 15.5 per cell and 4.2 per
-  // cut are on bisectors.  A quarter more for the ends of the waves' chunks.
+  // First sizes: 8 pieces per site and 3 per simplex, with 10 faces and 16 corners
+  // each.  n convex cells and m simplices that overlay each other meet in about n + m
+  // + 6 (n^2/3 m^1/3 + n^1/3 m^2/3) pieces (the two cross terms come from cells
+  // crossing simplex faces and simplices crossing cell faces; 5.4 to 5.7 was measured
+  // on uniform sites), which is more where n and m are alike: the records of the
+  // pieces themselves, 92 bytes each, get that and a quarter for the ends of the waves'
+  // chunks.  Their faces and corners (6 and 8 a piece there) have room as it is: 1M
+  // clustered sites take 8.27 GB (11.3 when they grew as well).
   const double cn = (double)n, cm = (double)dom->m;
   const double pieces = dom->dim == 3 ? cn + cm + 6.0 * (std::cbrt(cn * cn * cm) + std::cbrt(cn * cm * cm)) : 0.0;
+  const int64_t base = 8 * n + 3 * dom->m + 1024;
   // Few items to a wave: arenas of twice that, so that a wave takes half its share
   // at a time (`div` below).  Every refill is an atomic on one line that all
   // waves share, and in a clip this short they wait for it: 4,099 sites with
@@ -890,13 +894,20 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
   const int64_t items = dom->dim == 3 ? n : dom->m;  // sites, or triangles
   const bool few = items <= 8 * (int64_t)(dom->dim == 3 ? vd_sweep_workgroups(n) : vd_tri_workgroups(dom->m));
   const int64_t room = few ? 2 : 1;
-  want.piece = std::max<int64_t>(c->d.cap_piece, room * std::max<int64_t>(8 * n + 3 * dom->m + 1024, (int64_t)(1.25 * pieces) + 1024));
-  want.nbr = std::max<int64_t>(c->d.cap_nbr, room * (20 * n + 1024));
   // surfaces always keep the edge flags of their pieces (the per-site pass reads them)
   const bool keep_faces = opt.emit_polytopes || dom->dim == 2;
-  want.face = keep_faces ? std::max<int64_t>(c->d.cap_face, 10 * want.piece) : 0;
-  want.vert = keep_faces ? std::max<int64_t>(c->d.cap_vert, 16 * want.piece) : 0;
-  want.fint = opt.want_grad ? std::max<int64_t>(c->d.cap_fint, std::max<int64_t>(4 * want.piece, room * ((int64_t)(1.25 * (15.5 * cn + 4.2 * pieces)) + 1024))) : 0;
+  auto sizes = [&](int64_t piece, int64_t room) {
+    want.piece = std::max<int64_t>(c->d.cap_piece, room * piece);
+    want.nbr = std::max<int64_t>(c->d.cap_nbr, room * (20 * n + 1024));
+    want.face = keep_faces ? std::max<int64_t>(c->d.cap_face, 10 * room * base) : 0;
+    want.vert = keep_faces ? std::max<int64_t>(c->d.cap_vert, 16 * room * base) : 0;
+    want.fint = opt.want_grad ? std::max<int64_t>(c->d.cap_fint, 4 * room * base) : 0;
+  };
+  sizes(std::max<int64_t>(base, (int64_t)(1.25 * pieces) + 1024), room);
+  // face moments are per cell inside M and per piece elsewhere: 15.5 faces of a cell
+  // and 4.2 of a cut are on bisectors, and in a small clip most cells meet the boundary
+  if (few && opt.want_grad)
+    want.fint = std::max<int64_t>(want.fint, room * ((int64_t)(1.25 * (15.5 * cn + 4.2 * pieces)) + 1024));
   if (opt.no_sync) {
     // no allocation: the arenas keep the sizes of the synchronous clip before
     want.piece = c->d.cap_piece; want.nbr = c->d.cap_nbr;
@@ -906,6 +917,10 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
   }
   for (int attempt = 0; attempt < 8; attempt++) {
     hipError_t e = alloc_cells(c, n, want);
+    if (e == hipErrorOutOfMemory && attempt == 0 && !opt.no_sync) {
+      sizes(base, 1);  // the least
+      e = alloc_cells(c, n, want);
+    }
     if (e != hipSuccess) {
       c->status = e == hipErrorOutOfMemory ? VD_ERR_OUT_OF_MEMORY : VD_ERR_HIP;
       return fail((vd_status)c->status, "vd_clip_cells: %s", hipGetErrorString(e));

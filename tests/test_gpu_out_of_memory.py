@@ -134,3 +134,23 @@ def test_kept_blocks_are_given_back_on_demand():
     log(f"kept {held}, after release {left}")
     assert held > 1 << 28 and left < 4 << 20
     del keep
+
+
+def test_first_sizes():
+    """Faces (4 bytes, 10 a piece) and corners (36 bytes, 16 a piece) take the room of 8
+    pieces per site and 3 per simplex also where sites and simplices are alike in
+    number and the pieces get more: what a clip with them holds beyond one without."""
+    import paper_2509_07175_amd as vd
+    dom = vd.Domain.from_vdgen(vdgen.kuhn_cube_grid(22))
+    n = 64000
+    g = vd.build_grid(_sites(n), bbox=(0, 0, 0, 1, 1, 1))
+    used = {}
+    for emit in (1, 1, 0):  # (the first clip leaves the runtime's scratch memory behind)
+        c = None
+        vd.release_memory()
+        free = _free()
+        c = vd.clip_cells(g, dom, vd.Options.default(emit_polytopes=emit))
+        used[emit] = free - _free()
+    base = 8 * n + 3 * dom.m + 1024
+    log(f"n={n} m={dom.m} {used} {base * (10 * 4 + 16 * 36)}")
+    assert used[1] - used[0] < 1.01 * base * (10 * 4 + 16 * 36) + (8 << 20) and c.info()["n_pieces"] > base
