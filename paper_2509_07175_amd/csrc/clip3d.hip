@@ -808,8 +808,8 @@ __device__ __forceinline__ void init_box(WaveLds &S, const SiteCtx &X, const dou
 // Strang and Fix (centroid -27/48, points (3/5,1/5,1/5) 25/48); with a density
 // every integrand carries it and one degree-5 rule takes all twelve.
 template <bool DENS>
-__device__ __forceinline__ void face_moments(WaveLds &S, int nc, int npl, uint64_t fmask, const CellsDev &C, const GridView &G,
-                             const SiteCtx &X, long long pidx) {
+__device__ __forceinline__ void face_moments(WaveLds &S, int nc, int npl, uint64_t pos, const CellsDev &C, const GridView &G,
+                             const SiteCtx &X, long long pidx, long long base) {
   const int l = vd_lane();
   __syncthreads();
   if (l < npl) S.pfirst[l] = 0x7fffffff;
@@ -821,10 +821,8 @@ __device__ __forceinline__ void face_moments(WaveLds &S, int nc, int npl, uint64
     atomicMin(&S.pfirst[p8(pl, 2)], s);
   }
   __syncthreads();
-  const bool mine = l < npl && ((fmask >> l) & 1ull) && S.plab[l] >= 0;
-  const uint64_t pos = __ballot(mine);
+  const bool mine = (pos >> l) & 1ull;
   const int npos = __popcll(pos);
-  const long long base = arena_take(S.ar, C, AR_FINT, npos);
   const bool fits = base + npos <= C.cap_fint;
   if (l == 0 && pidx < C.cap_piece) {
     GL(C.piece_fint_start)[pidx] = base;
@@ -1337,13 +1335,10 @@ __device__ __forceinline__ void do_site(WaveLds &S, const GridView &G0, const Do
     if (MON) count_add(S.ar.fantets, 3 * nc);
     // ---- emit the piece ----
     const int nface = __popcll(fmask);
-    const long long pidx = arena_take(S.ar, C, AR_PIECE, 1);
-    long long fo = 0, vo = 0;
-    if (C.emit) {
-      fo = arena_take(S.ar, C, AR_FACE, nface);
-      vo = arena_take(S.ar, C, AR_VERT, nc);
-    }
-    if (C.want_grad) face_moments<DENS>(S, nc, npl, fmask, C, G, X, pidx);
+    const uint64_t bis = C.want_grad ? __ballot(l < npl && ((fmask >> l) & 1ull) && S.plab[l] >= 0) : 0ull;
+    const long long at = arena_take_all(S.ar, C, arena_counts(1, C.emit ? nface : 0, C.emit ? nc : 0, __popcll(bis)));
+    const long long pidx = readlane_ll(at, AR_PIECE), fo = readlane_ll(at, AR_FACE), vo = readlane_ll(at, AR_VERT);
+    if (C.want_grad) face_moments<DENS>(S, nc, npl, bis, C, G, X, pidx, readlane_ll(at, AR_FINT));
     // a record that does not fit its arena is dropped and counted; the per-site
     // counts below only count what was written, so the CSR built from them
     // stays inside the arenas (the clip then reports VD_ERR_CAPACITY)
@@ -1466,13 +1461,13 @@ __device__ __forceinline__ void do_site(WaveLds &S, const GridView &G0, const Do
 // CORNERS: the interior split by the cells' corners (whole_interior on a
 // convex domain).  Each is compiled in only for the instances that use it, so
 // the default instance carries none of them.
-template <bool MON, bool DENS, bool POW, bool CORNERS>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) site_kernel(GridView G, DomainView D, const CellsDev *__restrict__ Cp, int redo) {
+template <bool MON, bool DENS, bool POW, bool CORNERS, bool REDO>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) site_kernel(GridView G, DomainView D, const CellsDev *__restrict__ Cp) {
   __shared__ WaveLds S;
   const CellsDev &C = *Cp;
   arena_init(S.ar);
   for (;;) {
-    const int si = redo ? redo_next(C) : queue_next(S.ar, C, G.n);
+    const int si = REDO ? redo_next(C) : queue_next(S.ar, C, G.n);
     if (si < 0) break;
     // the site's own diagram (a batch) or the only one; one call site keeps
     // the per-site code inlined once
@@ -1511,7 +1506,7 @@ int resident_workgroups() {
   int &w = cache[dev];
   if (!w) {
     int per_cu = 0, ncu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, site_kernel<false, false, false, false>, 64, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, site_kernel<false, false, false, false, false>, 64, 0) != hipSuccess ||
         per_cu < 1)
       per_cu = 1;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) ncu = 1;
@@ -1542,21 +1537,30 @@ void vd_launch_clip_begin(unsigned long long *cnt, int *queue, long long items, 
 void vd_launch_sites3d(const GridView &G, const DomainView &D, const CellsDev *Cdev, int workgroups, bool monitor,
                        bool density, bool power, bool corners, bool redo, hipStream_t st) {
   const dim3 grid(workgroups), block(64);
+#define VD_SITES(mon, dens, pow, corners, redo_) \
+  hipLaunchKernelGGL((site_kernel<mon, dens, pow, corners, redo_>), grid, block, 0, st, G, D, Cdev)
+#define VD_SITES_REDO(mon, dens, pow, corners)      \
+  do {                                              \
+    if (redo) VD_SITES(false, dens, pow, corners, true); \
+    else VD_SITES(mon, dens, pow, corners, false);  \
+  } while (0)
   if (power) {  // power diagrams: no density, interior split by the boundary diagram
-    if (monitor) hipLaunchKernelGGL((site_kernel<true, false, true, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
-    else hipLaunchKernelGGL((site_kernel<false, false, true, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    if (monitor) VD_SITES(true, false, true, false, false);
+    else VD_SITES_REDO(false, false, true, false);
   } else if (corners) {
-    if (monitor && density) hipLaunchKernelGGL((site_kernel<true, true, false, true>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
-    else if (monitor) hipLaunchKernelGGL((site_kernel<true, false, false, true>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
-    else if (density) hipLaunchKernelGGL((site_kernel<false, true, false, true>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
-    else hipLaunchKernelGGL((site_kernel<false, false, false, true>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    if (monitor && density) VD_SITES(true, true, false, true, false);
+    else if (monitor) VD_SITES(true, false, false, true, false);
+    else if (density) VD_SITES_REDO(false, true, false, true);
+    else VD_SITES_REDO(false, false, false, true);
   } else if (monitor && density) {
-    hipLaunchKernelGGL((site_kernel<true, true, false, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    VD_SITES(true, true, false, false, false);
   } else if (monitor) {
-    hipLaunchKernelGGL((site_kernel<true, false, false, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    VD_SITES(true, false, false, false, false);
   } else if (density) {
-    hipLaunchKernelGGL((site_kernel<false, true, false, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    VD_SITES_REDO(false, true, false, false);
   } else {
-    hipLaunchKernelGGL((site_kernel<false, false, false, false>), grid, block, 0, st, G, D, Cdev, redo ? 1 : 0);
+    VD_SITES_REDO(false, false, false, false);
   }
+#undef VD_SITES_REDO
+#undef VD_SITES
 }
