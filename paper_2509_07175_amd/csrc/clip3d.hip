@@ -95,7 +95,27 @@ struct Stats {
   long long queries = 0, cands = 0, clips = 0, grid = 0;  // grid: queries not answered by the site cache
 };
 
-
+// A corner T that is fixed to less than kSure, on the edge from A (outside the plane
+// n.y = c) to B (inside).  It can lie past the ends, out of order with the planes
+// before, or anywhere: on regular lattices of sites (cubic, BCC, FCC, hexagonal, turned
+// cubic) single cells were off by any factor at noise of 1e-16, and by 1e-17 / noise
+// above that.  So it is placed on the edge, whose ends lie on either side of the
+// plane, except between the ends, near the plane and from kFair on: an edge has the
+// rounding of its ends, and around a dense cluster of sites, where planes are near and
+// corners far, that moved them by up to 1e-7 and Cramer's rule by 2e-10 (fixed to 25
+// digits at worst, and off the plane by 9e-10 of the edge).
+constexpr unsigned kFair = 25;
+__device__ __forceinline__ void keep_on_edge(const double *A, const double *B, const double *n, double c, bool fair, double *T) {
+  const double e[3] = {B[0] - A[0], B[1] - A[1], B[2] - A[2]};
+  const double ue = (T[0] - A[0]) * e[0] + (T[1] - A[1]) * e[1] + (T[2] - A[2]) * e[2];
+  const double ee = e[0] * e[0] + e[1] * e[1] + e[2] * e[2], nn = n[0] * n[0] + n[1] * n[1] + n[2] * n[2];
+  const double r = n[0] * T[0] + n[1] * T[1] + n[2] * T[2] - c;
+  if (fair && ue >= 0.0 && ue <= ee && r * r <= 2.25e-18 * nn * ee) return;
+  const double da = n[0] * A[0] + n[1] * A[1] + n[2] * A[2] - c, db = n[0] * B[0] + n[1] * B[1] + n[2] * B[2] - c;
+  const double t = da > db ? fmin(da / (da - db), 1.0) : 1.0;  // (B can be outside as well, of another part)
+#pragma unroll
+  for (int x = 0; x < 3; x++) T[x] = A[x] + t * e[x];
+}
 
 // Vertex of three planes by Cramer's rule, planes taken in ascending flag order
 // so a vertex does not depend on the order in which its planes were created.
