@@ -1093,8 +1093,8 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
     if (opt.time_kernels) HIP_TRY(hipEventRecord(c->ev1, st));
     HIP_TRY(hipGetLastError());
     // what the sweep left: usually nothing, and rarely much on solids.  A wave for
-    // each item up to the resident ones (4,096 cells of 60 faces among 250,000: 9.6 against 17.8 ms
-    // with 512 waves); a no-sync clip cannot look, and takes 512 on solids.
+    // each item up to the resident ones (4,096 cells of 60 faces among 250,000: 9.6
+    // against 17.8 ms with 512 waves); a no-sync clip cannot look, and launches all.
     auto rest = [&](int64_t items_left) {
       if (dom->dim == 2) {
         vd_launch_void_triangles(c->d_dev, st);
@@ -1107,7 +1107,7 @@ vd_status vd_clip_cells(vd_grid g, vd_domain dom, const vd_options *opt_in, void
       }
     };
     if (opt.no_sync) {
-      if (sweep) rest(dom->dim == 2 ? dom->m : 512);
+      if (sweep) rest(items);
       // stream-ordered only: finalize from the device counters, copy them to
       // pinned host memory, and check them in vd_cells_info
       c->pending = true;

@@ -1487,7 +1487,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3)))
   const CellsDev &C = *Cp;
   arena_init(S.ar);
   for (;;) {
-    const int si = REDO ? redo_next(C) : queue_next(S.ar, C, G.n);
+    const int si = REDO ? redo_next(S.ar, C) : queue_next(S.ar, C, G.n);
     if (si < 0) break;
     // the site's own diagram (a batch) or the only one; one call site keeps
     // the per-site code inlined once

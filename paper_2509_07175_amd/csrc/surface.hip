@@ -717,7 +717,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
   const CellsDev &C = *Cp;
   arena_init(S.ar);
   for (;;) {
-    const int a = redo ? redo_next(C) : queue_next(S.ar, C, D.m);
+    const int a = redo ? redo_next(S.ar, C) : queue_next(S.ar, C, D.m);
     if (a < 0) break;
     // the triangle's own diagram (a batch) or the only one
     const int b = D.nb > 1 ? diagram_of(D.simp_off, D.nb, a) : 0;

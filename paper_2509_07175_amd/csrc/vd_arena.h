@@ -109,13 +109,17 @@ __device__ __forceinline__ int queue_next(WaveArena &A, const CellsDev &C, long 
   return __builtin_amdgcn_readlane(r, 0);
 }
 
-// Next site of the list that the sweep kernel left (complete when this runs),
-// or -1.
-__device__ __forceinline__ int redo_next(const CellsDev &C) {
+// Next item of the list that the sweep kernel left (complete when this runs), or
+// -1.  A wave's first one is its own number, the others follow by atomics: waves
+// beyond the list's end, usually all of them, read its length and are done.
+__device__ __forceinline__ int redo_next(WaveArena &A, const CellsDev &C) {
   int r = -1;
   if (vd_lane() == 0) {
     const int n = (int)GL(C.cnt)[CNT_REDO];
-    const int v = __hip_atomic_fetch_add(GL(C.queue) + VD_QREDO * VD_QSTRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int v = blockIdx.x;
+    if (A.qi && v < n)
+      v = gridDim.x + __hip_atomic_fetch_add(GL(C.queue) + VD_QREDO * VD_QSTRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    A.qi = 1;
     if (v < n) r = GL(C.redo)[v];
   }
   return __builtin_amdgcn_readlane(r, 0);
