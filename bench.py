@@ -21,7 +21,10 @@ sys.path.insert(0, ROOT)
 
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # MI355X dense FP64 vector
 HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
-# algorithmic FP64 work per unit; every unit is counted on the device (vd_cells_info)
+# FP64 work of the sweep kernel, an estimate: sites tested, clips, pieces and corners are
+# counted on the device (vd_cells_info), but a tested site is taken to meet as many corners
+# as the cell has in the end, a clip to make 5 corners, and a piece of v corners to be
+# 2 v - 14 tetrahedra
 FLOPS_PER_TEST = 6               # n.y > c of one corner against a site's bisector: 1 mul, 2 fma, 1 compare
 FLOPS_PER_NEW_CORNER = 51        # Cramer solve of three planes: 3 cross products (27), det (5),
                                  # reciprocal (1), 3 coordinates (18)
@@ -544,9 +547,8 @@ def main():
     vd.clip_cells(grid, d, mopts, cells=mcells)
     minfo = mcells.info()
     del mcells
-    # the dominant kernel: the persistent per-site kernel (cell and pieces).  Every
-    # site it tests is tested against all corners of the cell (queries: final
-    # corners), and a piece of v corners is about 2 v - 14 tetrahedra.
+    # the dominant kernel: the persistent per-site kernel (cell and pieces); its work is
+    # estimated as said at FLOPS_PER_TEST (queries: the cells' final corners)
     dom_ms = float(np.mean(kern))
     dom_name = "sweep_kernel"
     if args.carve_mode != 1 or args.improved or args.straddle or not args.site_cache:
@@ -580,6 +582,7 @@ def main():
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / FP64_VECTOR_PEAK_TFLOPS, "traffic": traffic,
                      "kernel": dom_name, "kernel_ms": dom_ms, "algorithmic_flops": flops,
+                     "algorithmic_flops_are": "estimated from counted sites, clips, pieces and corners",
                      "hbm": {"algorithmic_bytes": alg_bytes,
                              "achieved": alg_bytes / (dom_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                              "frac": alg_bytes / (dom_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,

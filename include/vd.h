@@ -7,11 +7,15 @@
  * domain-cell intersection P_{a,i} = T_a intersected with the Voronoi cell
  * Omega_i (Sec. 3.1, Eq. 1), with the face flags of Sec. 3.2, and per site the
  * mass, centroid and CVT energy integrand (Sec. 7.4, Eq. 3, density 1).
- * Each piece is carved by point-in-cell tests (Sec. 4.1, Eq. 2) and the
- * edge-based bisector search (Sec. 4.2, improved as in Sec. 6.1) on straddling
- * or virtual edges (Alg. 1 and Alg. 3), the clip removing only the connected
- * outside component R_p (Sec. 6.3).  Nearest-site queries use a uniform grid
- * built by counting sort (Sec. 6.2).
+ * Each piece is found by point-in-cell tests (Sec. 4.1, Eq. 2).  By default a
+ * solid's cell is cut by the nearby sites in order of distance, all its corners
+ * tested against one site at a time, and a piece is that cell cut by its
+ * tetrahedron; on surfaces a polygon's corners are tested against the sites
+ * around the triangle.  With search options other than the defaults, and for
+ * cells that this leaves, it is the edge-based bisector search (Sec. 4.2,
+ * improved as in Sec. 6.1) on straddling or virtual edges (Alg. 1 and Alg. 3),
+ * the clip removing only the connected outside component R_p (Sec. 6.3).
+ * Nearest-site queries use a uniform grid built by counting sort (Sec. 6.2).
  *
  * Conventions shared by every entry point
  *  - C linkage; only plain types cross the boundary.  Pointers named *_host

@@ -21,25 +21,25 @@
 // the new corners their free lanes, so survivors never move.  Planes and
 // the tables that link the fan of a new face are in LDS.
 //
-// What bounds it: waits for LDS round trips (45 % of a wave's time) and VALU
-// issue (65 % of the cycles), at four waves per SIMD (128 VGPRs; five waves at 96
-// spill: 26.0 against 24.6 ms on the 1M clustered workload, 58.8 against 57.7 on 5M
-// uniform sites).  So reads that do not depend on each other are issued
-// together: the planes of four sites before their tests, the planes of a new
-// corner before the tables that link it, those of up to seven tetrahedra for one
-// chain of mesh reads; and rows of LDS are 16-byte aligned (5M sites 57.7 -> 53.5 ms,
-// 1M clustered 24.6 -> 23.3 ms).  Two pieces at once, one in each half of the wave,
-// or corners placed along the cut edge instead of solved for, gained nothing.
+// What bounds it: waits for LDS round trips (two fifths of a wave's time) and VALU
+// issue (three fifths of the cycles), at four waves per SIMD (128 VGPRs).  1M clustered
+// sites in 750,000 tetrahedra take 22 ms, 5M uniform sites 50 (searched carve: 64.7 and
+// 168.6).  Figures for a choice, here and below, are of the two sides in one tree at the
+// time: five waves at 96 VGPRs spill, 26.0 against 24.6 ms on the clustered sites and
+// 58.8 against 57.7 on the uniform ones.  Reads that do not depend on each other are
+// issued together: the planes of four sites before their tests, the planes of a new
+// corner before the tables that link it, those of up to seven tetrahedra for one chain
+// of mesh reads; and rows of LDS are 16-byte aligned (57.7 -> 53.5 ms uniform, 24.6 ->
+// 23.3 clustered).  Two pieces at once, one in each half of the wave, or corners placed
+// along the cut edge instead of solved for, gained nothing.
 // All control flow is on scalar values (ballots, readlane): where the compiler
 // cannot see that a value is uniform it is passed through readlane, or every
-// branch behind it would save and restore the exec mask (36 -> 28 ms on the 1M
-// clustered workload).  Against the searched carve: 1M clustered sites in
-// 750,000 tetrahedra 64.7 -> 23 ms, 5M uniform sites 168.6 -> 51 ms.
+// branch behind it would save and restore the exec mask (36 -> 28 ms clustered).
 //
-// A cell that does not fit (more than 64 corners or 36 planes at a time) or
-// whose cut is degenerate is put on a list that clip3d.hip's kernel works
-// through afterwards; options other than the defaults of the search go there
-// as a whole.
+// A cell that does not fit (more than 64 corners or 36 planes at a time), whose cut
+// is degenerate or that has a corner which its planes hardly fix is put on a list that
+// clip3d.hip's kernel works through afterwards; options other than the defaults of the
+// search go there as a whole.
 #include "vd_site.h"
 #include "vd_sweep.h"
 
@@ -789,8 +789,8 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     // |x - v_i|^2).  With a density, four Lloyd steps of 60,000
     // sites: 15.1 ms with 15 points in three tetrahedra per corner (the planes'
     // feet and three edges, 26 lanes at work), 8.7 ms here; without one the
-    // chain of LDS round trips is what it costs either way (25.7 ms of 26.3 on
-    // the 1M clustered workload) ----
+    // chain of LDS round trips is what it costs either way (25.7 against 26.3 ms
+    // on the 1M clustered workload) ----
     const uint64_t fmask = faces_of(S, Q);
     uint64_t bis = GRAD ? fmask & cellpos : 0ull;  // its bisector faces
     const bool live = in_mask(Q.M);

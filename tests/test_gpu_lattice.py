@@ -115,9 +115,11 @@ def test_lattice_cells(name, noise):
         s = torch.as_tensor(sites, dtype=torch.float64, device="cuda")
         d = vd.Domain.from_vdgen(dom)
         g = vd.build_grid(s, bbox=(0.0, 0.0, 0.0, 1.0, 1.0, 1.0))
-        for opts in ({}, {"want_grad": 1}, {"whole_interior": 1}):
+        # (equal weights: the same cells as a power diagram)
+        w = vd.build_grid(s, bbox=(0.0, 0.0, 0.0, 1.0, 1.0, 1.0), weights=torch.full((len(sites),), 0.25, device="cuda", dtype=torch.float64))
+        for grid, opts in ((g, {}), (g, {"want_grad": 1}), (g, {"whole_interior": 1}), (w, {}), (g, {"improved_search": 1})):
             try:
-                c = vd.clip_cells(g, d, vd.Options.default(**opts))
+                c = vd.clip_cells(grid, d, vd.Options.default(**opts))
             except vd.VDError as e:
                 log(f"{name} noise {noise} m={dom.m} {opts}: {e}")
                 assert e.status in (4, 5) and noise < 1e-12
