@@ -423,7 +423,9 @@ __device__ __forceinline__ uint64_t faces_of(SweepLds &S, const Poly &Q) {
 }
 
 // Lists the triangles (lowest corner, corner, next corner) of the faces that do
-// not hold corner `apex`; returns their number (124 at most).
+// not hold corner `apex` (LOW: it is the lowest one); returns their number (124 at
+// most).
+template <bool LOW>
 __device__ __forceinline__ int list_triangles(SweepLds &S, const Poly &Q, int apex) {
   const int l = vd_lane(), at = __builtin_amdgcn_readlane(Q.cp, apex);
   int T = 0;
@@ -431,7 +433,8 @@ __device__ __forceinline__ int list_triangles(SweepLds &S, const Poly &Q, int ap
   for (int e = 0; e < 3; e++) {
     // plane e of the corner continues around its face to the corner across edge e + 2
     const int p = p8(Q.cp, e), nx = across(Q, e == 0 ? 2 : e - 1), s = S.F.pfirst[p];
-    const uint64_t act = lanes((p != p8(at, 0)) & (p != p8(at, 1)) & (p != p8(at, 2)) & (s != l) & (s != nx)) & Q.M;
+    const bool apart = LOW ? s != apex : (p != p8(at, 0)) & (p != p8(at, 1)) & (p != p8(at, 2));
+    const uint64_t act = lanes(apart & (s != l) & (s != nx)) & Q.M;
     if (in_mask(act)) S.F.tri[T + mbcnt64(act)] = (unsigned)(s | l << 8 | nx << 16);
     T += __popcll(act);
   }
@@ -783,10 +786,11 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     // ---- moments of the piece: tetrahedra of a corner o and the triangles of
     // the faces that do not hold it (about 40, one to a lane), in coordinates
     // relative to o, so that the rounding error scales with the piece and not
-    // with its distance to v_i.  o is the corner nearest to v_i: the energy is moved
-    // there from o by terms that cancel where |o| is large (errors of the pieces of
-    // uniform cells 2.8e-16 on average, 6.0e-16 from any corner, 3.7e-16 from sums of
-    // |x - v_i|^2).  With a density, four Lloyd steps of 60,000
+    // with its distance to v_i.  Only the volume's, that is: first moments and energy
+    // are summed about v_i, or with a density about o and moved there by terms that
+    // cancel where |o| is large, so o is the corner nearest to v_i then (errors of the
+    // energy of uniform cells' pieces 3.7e-16 on average, with a density 3.2e-16 and
+    // 6.6e-16 from any corner).  With a density, four Lloyd steps of 60,000
     // sites: 15.1 ms with 15 points in three tetrahedra per corner (the planes'
     // feet and three edges, 26 lanes at work), 8.7 ms here; without one the
     // chain of LDS round trips is what it costs either way (25.7 against 26.3 ms
@@ -801,11 +805,19 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
     if (late) {
       fb = arena_take(S.ar, C, AR_FINT, __popcll(bis));
     } else {
-      const int far = in_mask(Q.M) ? __double2hiint(Q.y0 * Q.y0 + Q.y1 * Q.y1 + Q.y2 * Q.y2) : 0x7fffffff;
-      const int apex = __ffsll((unsigned long long)lanes(far == -wave_imax(-far))) - 1;
+      int apex = __ffsll((unsigned long long)Q.M) - 1;
+      if (DENS) {
+        const int far = live ? __double2hiint(Q.y0 * Q.y0 + Q.y1 * Q.y1 + Q.y2 * Q.y2) : 0x7fffffff;
+        apex = __ffsll((unsigned long long)lanes(far == -wave_imax(-far))) - 1;
+      }
       const double o0 = readlane_d(Q.y0, apex), o1 = readlane_d(Q.y1, apex), o2 = readlane_d(Q.y2, apex);
-      if (live) { S.F.y[l][0] = Q.y0 - o0; S.F.y[l][1] = Q.y1 - o1; S.F.y[l][2] = Q.y2 - o2; }
-      const int T = list_triangles(S, Q, apex);
+      if (live) {
+        S.F.y[l][0] = DENS ? Q.y0 - o0 : Q.y0;
+        S.F.y[l][1] = DENS ? Q.y1 - o1 : Q.y1;
+        S.F.y[l][2] = DENS ? Q.y2 - o2 : Q.y2;
+      }
+      const int T = list_triangles<!DENS>(S, Q, apex);
+      const double oo = o0 * o0 + o1 * o1 + o2 * o2;
       double dm = 0;  // (DENS: the moments are weighted, pv is the volume)
       ConeDensity cd;
       if (DENS) cd = cone_density(C.dens, X.vx + o0, X.vy + o1, X.vz + o2);
@@ -814,7 +826,10 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
         if (t0 + l < T) {
           const unsigned tri = S.F.tri[t0 + l];
           const double *P = S.F.y[tri & 255], *Y = S.F.y[(tri >> 8) & 255], *Z = S.F.y[tri >> 16];
-          const double p[3] = {P[0], P[1], P[2]}, y[3] = {Y[0], Y[1], Y[2]}, z[3] = {Z[0], Z[1], Z[2]};
+          const double P0 = P[0], P1 = P[1], P2 = P[2], Y0 = Y[0], Y1 = Y[1], Y2 = Y[2], Z0 = Z[0], Z1 = Z[1], Z2 = Z[2];
+          const double p[3] = {DENS ? P0 : P0 - o0, DENS ? P1 : P1 - o1, DENS ? P2 : P2 - o2};
+          const double y[3] = {DENS ? Y0 : Y0 - o0, DENS ? Y1 : Y1 - o1, DENS ? Y2 : Y2 - o2};
+          const double z[3] = {DENS ? Z0 : Z0 - o0, DENS ? Z1 : Z1 - o1, DENS ? Z2 : Z2 - o2};
           // 6 vol of (0, p, y, z)
           const double det = p[0] * (y[1] * z[2] - y[2] * z[1]) - p[1] * (y[0] * z[2] - y[2] * z[0]) +
                              p[2] * (y[0] * z[1] - y[1] * z[0]);
@@ -822,10 +837,10 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
           if (DENS) {
             cone_density_moments(cd, p, y, z, det, dm, pmx, pmy, pmz, pe);
           } else {
-            const double s0 = p[0] + y[0] + z[0], s1 = p[1] + y[1] + z[1], s2 = p[2] + y[2] + z[2];
+            const double s0 = o0 + P0 + Y0 + Z0, s1 = o1 + P1 + Y1 + Z1, s2 = o2 + P2 + Y2 + Z2;
             pmx += det * s0; pmy += det * s1; pmz += det * s2;
-            pe += det * (p[0] * p[0] + p[1] * p[1] + p[2] * p[2] + y[0] * y[0] + y[1] * y[1] + y[2] * y[2] +
-                         z[0] * z[0] + z[1] * z[1] + z[2] * z[2] + s0 * s0 + s1 * s1 + s2 * s2);
+            pe += det * (oo + P0 * P0 + P1 * P1 + P2 * P2 + Y0 * Y0 + Y1 * Y1 + Y2 * Y2 + Z0 * Z0 + Z1 * Z1 + Z2 * Z2 +
+                         s0 * s0 + s1 * s1 + s2 * s2);
           }
         }
       }
@@ -843,11 +858,13 @@ __device__ __forceinline__ bool do_cell(SweepLds &S, const GridView &G, const Do
         if (whole) break;
         continue;
       }
-      // from o to v_i
       pv = dm * (1.0 / 6.0);
       pmx *= DENS ? 1.0 / 6.0 : 1.0 / 24.0; pmy *= DENS ? 1.0 / 6.0 : 1.0 / 24.0; pmz *= DENS ? 1.0 / 6.0 : 1.0 / 24.0;
-      pe = pe * (DENS ? 1.0 / 6.0 : 1.0 / 120.0) + 2.0 * (o0 * pmx + o1 * pmy + o2 * pmz) + (o0 * o0 + o1 * o1 + o2 * o2) * pv;
-      pmx += o0 * pv; pmy += o1 * pv; pmz += o2 * pv;
+      pe *= DENS ? 1.0 / 6.0 : 1.0 / 120.0;
+      if (DENS) {  // from o to v_i
+        pe += 2.0 * (o0 * pmx + o1 * pmy + o2 * pmz) + oo * pv;
+        pmx += o0 * pv; pmy += o1 * pv; pmz += o2 * pv;
+      }
       if (l == 0) { S.acc[0] += pv; S.acc[1] += pmx; S.acc[2] += pmy; S.acc[3] += pmz; S.acc[4] += pe; }
       // ---- emit the piece ----
       if (GRAD) {
