@@ -68,7 +68,7 @@ def test_a_domain_that_does_not_fit_leaves_nothing_behind():
     del g, dom
     big = _mesh(80)  # 3 M tetrahedra: 49 MB each of indices and adjacency, and three times that besides
     base = _free()
-    filler = _fill(32 << 20)
+    filler = _fill(128 << 20)
     with pytest.raises(vd.VDError) as e:
         vd.Domain(*big)
     assert e.value.status == OUT_OF_MEMORY
@@ -112,7 +112,7 @@ def test_kept_blocks_make_room_for_a_domain():
     del g, c
     big = _mesh(80)
     _free()
-    filler = _fill(32 << 20)
+    filler = _fill(128 << 20)
     d = vd.Domain(*big)  # fits in what the freed handles left
     del filler
     assert abs(d.info()["measure"] - 1.0) < 1e-9
